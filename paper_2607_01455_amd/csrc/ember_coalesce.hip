@@ -13,9 +13,11 @@
 //
 // Pipeline (all integer work is exact and order-independent; every floating
 // point sum has a fixed order):
-//   1. stable LSD radix sort of (id, position) pairs by id, 1-4 passes of up
-//      to 10 bits (digit histograms per tile, offsets, stable scatter ranked with
-//      wavefront ballots), so the positions of one id stay ascending;
+//   1. stable sort of (id, position) pairs by id, so the positions of one id
+//      stay ascending: up to 65536 tokens by counting every place (coal_rank,
+//      and coal_merge past 4096), larger batches by an LSD radix sort, 1-4
+//      passes of up to 10 bits (digit histograms per tile, offsets, stable
+//      scatter ranked with wavefront ballots);
 //   2. head flags of the sorted ids -> distinct ids, segment starts, and the
 //      segment number of every sorted entry;
 //   3. the sums: the sorted entries are cut into chunks of about L positions
@@ -26,12 +28,16 @@
 //      float64 partial rows; the chunks where such segments end are listed
 //      with the chunk each began in, and a last launch adds each one's pieces
 //      in chunk order.
+// (small batches take shorter chunks, so that their few rows spread over more
+// wavefronts: 1000 tokens x 1023 columns 24 -> 10 us.)
 // A segment of at most L positions is therefore summed exactly in ascending
 // position order; a longer one is summed in that order within each piece of L
 // positions and then piece by piece.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "ember_launch.h"
 
@@ -44,13 +50,16 @@ constexpr int kCoalItems = 4;                        // keys per thread per tile
 constexpr int kTile = kCoalThreads * kCoalItems;     // keys per tile
 constexpr int kMaxDigitBits = 10;
 constexpr int kMaxBins = 1 << kMaxDigitBits;         // digits of up to 10 bits
-constexpr int kInBlockOffsetTiles = 64;              // up to this many tiles the
-                                                     // scatter derives its own offsets
+constexpr int64_t kRankMaxTokens = 65536;            // up to this many tokens: sorted by coal_rank
+constexpr int64_t kRankOneTile = 4096;               // up to this many: in one tile
 constexpr int kRunRows = 16;                         // rows a wavefront holds at once
 constexpr int kMinChunkBatches = 3;                  // a chunk is at least this many batches
                                                      // (fewer, longer chunks: at 16384 tokens and
                                                      // D = 4096 every wavefront of the sums is then
                                                      // resident at once, six per SIMD)
+constexpr int64_t kSumWaveSlots = 6144;              // wavefronts of the sums the chip holds at once
+                                                     // (256 compute units x 4 SIMDs x 6)
+constexpr int64_t kFewChunks = 512;
 constexpr int kMaxChunks = 4096;                     // bound on the chunks ...
 constexpr int64_t kMaxPartialElems = (int64_t)1 << 25; // ... and on chunks x D
 constexpr int kColsPerLane = 4;                      // columns per lane (4 or 8)
@@ -68,7 +77,7 @@ struct SortPass {
     int bits;
     int ntiles;
     uint32_t* hist;           // [bins][ntiles] digit counts per tile
-    const uint32_t* offs;     // [bins][ntiles] exclusive offsets, or null (derived in the block)
+    const uint32_t* offs;     // [bins][ntiles] exclusive offsets
     uint32_t* tile_bad;       // first pass: 1 where the tile holds an id outside [0, V)
 };
 
@@ -176,7 +185,6 @@ __global__ __launch_bounds__(kCoalThreads) void coal_scatter(SortPass a) {
     // [group][digit]: the group's count of the digit, then the count in the
     // earlier groups of the tile (< kTile, so 16 bits)
     __shared__ uint16_t cnt[kGroups * kMaxBins];
-    __shared__ uint32_t scan_lds[kCoalWaves];
     const int bins = 1 << a.bits;
     const int tile = blockIdx.x;
     const int t = threadIdx.x;
@@ -198,37 +206,7 @@ __global__ __launch_bounds__(kCoalThreads) void coal_scatter(SortPass a) {
         }
     }
 
-    if (a.offs != nullptr) {
-        for (int b = t; b < bins; b += kCoalThreads) off[b] = a.offs[(int64_t)b * a.ntiles + tile];
-    } else {
-        // offset of digit b in this tile = keys of smaller digits in every tile
-        // + keys of digit b in earlier tiles; thread t owns digits
-        // [t * per, (t + 1) * per)
-        const int per = bins > kCoalThreads ? bins / kCoalThreads : 1;
-        uint32_t tot[kMaxBins / kCoalThreads], before[kMaxBins / kCoalThreads];
-        uint32_t mine = 0;
-        for (int q = 0; q < per; ++q) {
-            const int b = t * per + q;
-            tot[q] = 0;
-            before[q] = 0;
-            if (b < bins) {
-#pragma unroll 16
-                for (int k = 0; k < a.ntiles; ++k) {
-                    const uint32_t c = a.hist[(int64_t)b * a.ntiles + k];
-                    tot[q] += c;
-                    if (k < tile) before[q] += c;
-                }
-            }
-            mine += tot[q];
-        }
-        uint32_t all;
-        uint32_t excl = block_excl_scan(mine, scan_lds, &all);
-        for (int q = 0; q < per; ++q) {
-            const int b = t * per + q;
-            if (b < bins) off[b] = excl + before[q];
-            excl += tot[q];
-        }
-    }
+    for (int b = t; b < bins; b += kCoalThreads) off[b] = a.offs[(int64_t)b * a.ntiles + tile];
     {
         // clear the counts, two 16-bit entries per word
         uint32_t* c32 = reinterpret_cast<uint32_t*>(cnt);
@@ -277,6 +255,171 @@ __global__ __launch_bounds__(kCoalThreads) void coal_scatter(SortPass a) {
 }
 
 // ---------------------------------------------------------------------------
+// the sort of batches of up to kRankMaxTokens: places are counted
+// ---------------------------------------------------------------------------
+//
+// The place of position p in a sorted tile of the batch is the number of the
+// tile's positions with a smaller id, or the same id and a smaller position:
+// every place is counted on its own, with no exchange between blocks.  One
+// launch sorts each tile so (all of the batch when it is one tile); another
+// then adds, for every position, the counts of the other tiles from binary
+// searches in them.  16384 tokens of a 128256-row table: 5.7 + 5.2 us, against
+// 25.8 us in the four launches of the radix sort; 65536 tokens: 12.7 + 23.6
+// against 36 us in four (the compares grow with the square of the batch, so
+// larger ones keep the radix sort).  One tile of up to 4096: 4.1 us at 1000
+// tokens.  Tiles of 2048 balance the two launches: half as large doubles the
+// searches, twice as large the compares.
+
+// Ids are compared as uint32 clamped into [0, V); kNoKey is above all of them.
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;
+
+struct RankParams {
+    const int64_t* tok;
+    int P;
+    int64_t V;
+    int tile;                 // positions per tile (a multiple of kRankThreads)
+    int bits;                 // id bits
+    uint32_t* keys_out;       // each tile's ids in order, at the tile's own place in the batch
+    uint32_t* vals_out;       // and their positions
+    uint32_t* blk_bad;        // [ceil(P / kWave)]: 1 where the block holds an id outside [0, V)
+};
+
+constexpr int kRankWaves = 16;
+constexpr int kRankThreads = kRankWaves * kWave;
+
+// One block per 64 positions; wavefront w compares them with the w-th of the
+// 16 runs of the tile (NQ groups of 64 ids each, staged in LDS and read back
+// four at a time by all lanes at once).  Bound by two vector operations per
+// compare of 64 pairs, P * tile / 64 of them over the chip.  (Counting ballots
+// of 64 ids against one position needs one vector operation, but two of the
+// scalar unit, which a compute unit has one of: 26 us at 16384 x 16384.)
+template <int NQ>
+__global__ __launch_bounds__(kRankThreads) void coal_rank(RankParams a) {
+    __shared__ uint32_t ids[kRankWaves][NQ * kWave];
+    __shared__ uint32_t cnt[kRankWaves][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int pb = blockIdx.x;                  // this block's group of 64 positions
+    const int tile0 = pb * kWave / a.tile * a.tile;
+    const int g0 = tile0 / kWave + wave * NQ;   // first group of this wavefront's run
+    // every id is loaded (past the end: the last one) before the first is used
+    int64_t idq[NQ];
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) idq[j] = a.tok[min((g0 + j) * kWave + lane, a.P - 1)];
+    const int p = pb * kWave + lane;
+    const int64_t idp = a.tok[min(p, a.P - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+    auto key_of_id = [&](int64_t i) { return i < 0 ? 0u : (i >= a.V ? (uint32_t)(a.V - 1) : (uint32_t)i); };
+#pragma unroll
+    for (int j = 0; j < NQ; ++j)
+        ids[wave][j * kWave + lane] = (g0 + j) * kWave + lane < a.P ? key_of_id(idq[j]) : kNoKey;
+    const uint32_t kp = key_of_id(idp);
+    const uint64_t any_bad = __ballot(p < a.P && (idp < 0 || idp >= a.V));
+    // the run is read by the wavefront that wrote it
+    uint32_t n = 0;
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+        // equal ids count in the groups before the block's own
+        const uint32_t below = kp + (g0 + j < pb ? 1u : 0u);
+        const uint4* q4 = reinterpret_cast<const uint4*>(&ids[wave][j * kWave]);
+#pragma unroll
+        for (int q = 0; q < kWave / 4; ++q) {
+            const uint4 v = q4[q];
+            n += (v.x < below) + (v.y < below);
+            n += (v.z < below) + (v.w < below);
+        }
+    }
+    if (pb >= g0 && pb < g0 + NQ) {
+        // the block's own group: equal ids in lower lanes
+        uint64_t peers = ~0ull;
+        for (int b = 0; b < a.bits; ++b) {
+            const bool bit = (kp >> b) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        n += (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
+    }
+    cnt[wave][lane] = n;
+    __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    uint32_t place = 0;
+#pragma unroll
+    for (int w = 0; w < kRankWaves; ++w) place += cnt[w][lane];
+    if (p < a.P) {
+        a.keys_out[tile0 + place] = kp;
+        a.vals_out[tile0 + place] = (uint32_t)p;
+    }
+    if (lane == 0) a.blk_bad[pb] = any_bad != 0 ? 1u : 0u;
+}
+
+// Merges the sorted tiles: the place of an entry is its place in its own tile
+// plus, for every other tile, the number of smaller ids (in earlier tiles:
+// smaller or equal ones).  One block per 64 entries; its wavefronts share the
+// tiles, kMergeTiles of them staged in LDS at a time.
+struct MergeParams {
+    const uint32_t* keys_in;
+    const uint32_t* vals_in;
+    uint32_t* keys_out;
+    uint32_t* vals_out;
+    int P;
+    int ntiles;
+};
+
+constexpr int kRankTile = 2048;     // positions per tile of a batch of several tiles
+constexpr int kMergeWaves = 8;
+constexpr int kMergeThreads = kMergeWaves * kWave;
+constexpr int kMergeTiles = 8;      // tiles in LDS at a time: 64 KiB
+
+__global__ __launch_bounds__(kMergeThreads) void coal_merge(MergeParams a) {
+    __shared__ uint32_t ids[kMergeTiles * kRankTile];
+    __shared__ uint32_t cnt[kMergeWaves][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int e = blockIdx.x * kWave + lane;
+    const int own = blockIdx.x * kWave / kRankTile;
+    const uint32_t key = a.keys_in[min(e, a.P - 1)];
+    const uint32_t val = a.vals_in[min(e, a.P - 1)];
+    uint32_t n = 0;
+    for (int t0 = 0; t0 < a.ntiles; t0 += kMergeTiles) {
+        const int nt = min(kMergeTiles, a.ntiles - t0);
+        const int base = t0 * kRankTile;
+        const int words = nt * kRankTile;
+        if (t0 > 0) __syncthreads();   // the last round's searches are done
+        for (int x = threadIdx.x * 4; x < words; x += kMergeThreads * 4) {
+            uint4 v;
+            if (base + x + 4 <= a.P) {
+                v = *reinterpret_cast<const uint4*>(a.keys_in + base + x);
+            } else {
+                v.x = base + x < a.P ? a.keys_in[base + x] : kNoKey;
+                v.y = base + x + 1 < a.P ? a.keys_in[base + x + 1] : kNoKey;
+                v.z = base + x + 2 < a.P ? a.keys_in[base + x + 2] : kNoKey;
+                v.w = kNoKey;
+            }
+            *reinterpret_cast<uint4*>(&ids[x]) = v;
+        }
+        __syncthreads();
+        for (int t = wave; t < nt; t += kMergeWaves) {
+            if (t0 + t == own) continue;
+            const uint32_t below = key + (t0 + t < own ? 1u : 0u);
+            const uint32_t* s = ids + t * kRankTile;
+            int at = 0;
+#pragma unroll
+            for (int step = kRankTile / 2; step >= 1; step >>= 1) at += s[at + step - 1] < below ? step : 0;
+            at += s[at] < below ? 1 : 0;
+            n += (uint32_t)at;
+        }
+    }
+    cnt[wave][lane] = n;
+    __syncthreads();
+    if (threadIdx.x >= kWave || e >= a.P) return;
+    uint32_t place = (uint32_t)(e - own * kRankTile);
+#pragma unroll
+    for (int w = 0; w < kMergeWaves; ++w) place += cnt[w][lane];
+    a.keys_out[place] = key;
+    a.vals_out[place] = val;
+}
+
+// ---------------------------------------------------------------------------
 // distinct ids and segments of the sorted keys
 // ---------------------------------------------------------------------------
 
@@ -285,7 +428,7 @@ struct HeadParams {
     int64_t P;
     int ntiles;
     uint32_t* tilecnt;        // heads per tile
-    const uint32_t* tileoff;  // exclusive offsets, or null (derived in the block)
+    const uint32_t* tileoff;  // exclusive offsets
     uint32_t* uid;            // [P] segment number of every sorted entry
     uint32_t* seg_start;      // [n + 1]
     int64_t* idx;             // [n] the distinct ids
@@ -330,15 +473,7 @@ __global__ __launch_bounds__(kCoalThreads) void coal_heads_write(HeadParams a) {
     __shared__ uint32_t tile_base;
     const int64_t k0 = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kCoalItems;
     const uint32_t hb = head_bits(a.K, k0, a.P);
-    if (a.tileoff != nullptr) {
-        if (threadIdx.x == 0) tile_base = a.tileoff[blockIdx.x];
-    } else {
-        uint32_t s = 0;
-        for (int k = threadIdx.x; k < (int)blockIdx.x; k += kCoalThreads) s += a.tilecnt[k];
-        uint32_t total;
-        (void)block_excl_scan(s, lds, &total);
-        if (threadIdx.x == 0) tile_base = total;
-    }
+    if (threadIdx.x == 0) tile_base = a.tileoff[blockIdx.x];
     __syncthreads();
     uint32_t total;
     const uint32_t excl = block_excl_scan((uint32_t)__popc(hb), lds, &total);
@@ -367,6 +502,76 @@ __global__ __launch_bounds__(kCoalThreads) void coal_heads_write(HeadParams a) {
             *a.n_out = nbad ? -1 : (int64_t)n;   // -1: a device-count step refuses it
             *a.status = nbad ? 1 : 0;
         }
+    }
+}
+
+// The same in one launch, for the batches of coal_rank: a block of 1024
+// threads per 1024 sorted entries, one each, that counts the heads of all
+// earlier entries itself (16 per thread and round) instead of waiting for
+// another launch to do it: 4.3 us at 16384 tokens against 2.7 + 4.4 us.
+constexpr int kHeadThreads = 1024;
+constexpr int kHeadWaves = kHeadThreads / kWave;
+
+__global__ __launch_bounds__(kHeadThreads) void coal_heads_small(HeadParams a, int nbad) {
+    __shared__ uint32_t before_lds[kHeadWaves], own_lds[kHeadWaves], bad_lds[kHeadWaves];
+    const int t = threadIdx.x;
+    const int lane = t & (kWave - 1);
+    const int wave = t / kWave;
+    const int P = (int)a.P;
+    const int base = blockIdx.x * kHeadThreads;
+    const int k = base + t;
+    const bool valid = k < P;
+    const uint32_t key = a.K[min(k, P - 1)];
+    const uint32_t prev = a.K[min(max(k - 1, 0), P - 1)];
+    uint32_t earlier = 0;
+    for (int e = 16 * t; e < base; e += 16 * kHeadThreads) {
+        // base is a multiple of 16: the whole run lies before this block's
+        uint4 v[4];
+        const uint32_t p0 = a.K[max(e - 1, 0)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = reinterpret_cast<const uint4*>(a.K + e)[q];
+        earlier += e == 0 || v[0].x != p0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q > 0) earlier += v[q].x != v[q - 1].w;
+            earlier += (v[q].y != v[q].x) + (v[q].z != v[q].y) + (v[q].w != v[q].z);
+        }
+    }
+    uint32_t bad = 0;
+    if (blockIdx.x == gridDim.x - 1)
+        for (int b = t; b < nbad; b += kHeadThreads) bad |= a.tile_bad[b];
+    if (blockIdx.x == 0 && t == 0) *a.fix_count = 0;
+    const bool head = valid && (k == 0 || prev != key);
+    const uint64_t hm = __ballot(head);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) earlier += __shfl_xor(earlier, off, kWave);
+    const uint64_t bm = __ballot(bad != 0);
+    if (lane == 0) {
+        before_lds[wave] = earlier;
+        own_lds[wave] = (uint32_t)__popcll(hm);
+        bad_lds[wave] = bm != 0 ? 1u : 0u;
+    }
+    __syncthreads();
+    uint32_t u = 0, all = 0, any_bad = 0;
+#pragma unroll
+    for (int w = 0; w < kHeadWaves; ++w) {
+        u += before_lds[w] + (w < wave ? own_lds[w] : 0u);
+        all += before_lds[w] + own_lds[w];
+        any_bad |= bad_lds[w];
+    }
+    // heads up to and including this entry, less one: its segment number
+    u += (uint32_t)__popcll(hm & (~0ull >> (kWave - 1 - lane))) - 1u;
+    if (valid) {
+        if (head) {
+            a.idx[u] = (int64_t)key;
+            a.seg_start[u] = (uint32_t)k;
+        }
+        a.uid[k] = u;
+    }
+    if (blockIdx.x == gridDim.x - 1 && t == 0) {
+        a.seg_start[all] = (uint32_t)a.P;
+        *a.n_out = any_bad ? -1 : (int64_t)all;   // -1: a device-count step refuses it
+        *a.status = any_bad ? 1 : 0;
     }
 }
 
@@ -444,38 +649,10 @@ __device__ __forceinline__ uint32_t f32_bits_to_bf16(uint32_t w) {
     return (w + 0x7FFFu + ((w >> 16) & 1u)) >> 16;
 }
 
-template <typename GT>
-__device__ __forceinline__ void store_cols(void* G, int64_t ldg, uint32_t u, int64_t col, int64_t D,
-                                           const double (&x)[kColsPerLane]) {
-    GT* row = static_cast<GT*>(G) + (int64_t)u * ldg;
-#pragma unroll
-    for (int e = 0; e < kColsPerLane; ++e) {
-        if (col + e < D) {
-            if constexpr (sizeof(GT) == 4) row[col + e] = (float)x[e];
-            else row[col + e] = f64_to_bf16(x[e]);
-        }
-    }
-}
-
-template <typename UT>
-__device__ __forceinline__ void load_cols(const UT* row, int64_t col, int64_t D, bool valid,
-                                          typename Cols<UT>::raw& r) {
-    using raw = typename Cols<UT>::raw;
-    r = raw{};
-    if (!valid) return;
-    if (col + kColsPerLane <= D) {
-        r = *reinterpret_cast<const raw*>(row + col);
-    } else {
-        UT tmp[kColsPerLane] = {};
-        for (int e = 0; e < kColsPerLane; ++e)
-            if (col + e < D) tmp[e] = row[col + e];
-        r = *reinterpret_cast<const raw*>(tmp);
-    }
-}
-
 // Stores of one lane's 4 columns through a buffer resource whose length is the
-// row's D columns: the hardware drops the stores of lanes past the end (D is a
-// multiple of 4 where these are used), so no lane-divergent branch is needed.
+// row's whole groups of 4 columns: the hardware drops the stores of lanes past
+// it, so no lane-divergent branch is needed.  Where D is not a multiple of 4
+// (kExact false) the lane that holds the rest stores it element by element.
 constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit data format, gfx9 family
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(void* row, int64_t bytes) {
@@ -483,11 +660,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(void* row, int64_t by
 }
 
 // One lane's columns of row u of G, already in G's format (kWords words).
-template <typename GT>
+template <typename GT, bool kExact>
 __device__ __forceinline__ void buf_store_words(void* G, int64_t ldg, uint32_t u, int col, int64_t D,
                                                 const uint32_t (&w)[Cols<GT>::kWords]) {
     GT* row = static_cast<GT*>(G) + (int64_t)u * ldg;
-    const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, D * (int64_t)sizeof(GT));
+    const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, (kExact ? D : D / kColsPerLane * kColsPerLane) * (int64_t)sizeof(GT));
     using v4 = decltype(__builtin_amdgcn_raw_buffer_load_b128(rs, 0, 0, 0));
     using v2 = decltype(__builtin_amdgcn_raw_buffer_load_b64(rs, 0, 0, 0));
     constexpr int kW = Cols<GT>::kWords;
@@ -500,10 +677,20 @@ __device__ __forceinline__ void buf_store_words(void* G, int64_t ldg, uint32_t u
         static_assert(kW == 2, "4 bf16 columns per lane");
         __builtin_amdgcn_raw_buffer_store_b64(v2{w[0], w[1]}, rs, byte0, 0, 0);
     }
+    if constexpr (!kExact) {
+        if (col < D && col + kColsPerLane > D) {
+#pragma unroll
+            for (int e = 0; e < kColsPerLane - 1; ++e) {
+                if (col + e >= D) break;
+                if constexpr (sizeof(GT) == 4) row[col + e] = __uint_as_float(w[e]);
+                else row[col + e] = (GT)(w[e / 2] >> (16 * (e & 1)));
+            }
+        }
+    }
 }
 
 // A finished float64 sum, rounded once to G's type.
-template <typename GT>
+template <typename GT, bool kExact>
 __device__ __forceinline__ void buf_store_cols(void* G, int64_t ldg, uint32_t u, int col, int64_t D,
                                                const double (&x)[kColsPerLane]) {
     uint32_t w[Cols<GT>::kWords];
@@ -512,14 +699,14 @@ __device__ __forceinline__ void buf_store_cols(void* G, int64_t ldg, uint32_t u,
         if constexpr (sizeof(GT) == 4) w[e] = __float_as_uint((float)x[e]);
         else w[e] = (uint32_t)f64_to_bf16(x[2 * e]) | ((uint32_t)f64_to_bf16(x[2 * e + 1]) << 16);
     }
-    buf_store_words<GT>(G, ldg, u, col, D, w);
+    buf_store_words<GT, kExact>(G, ldg, u, col, D, w);
 }
 
 // A segment of one row: its sum is that row's value, which G's type holds
 // exactly when the types agree (else one rounding, fp32 -> bf16), so the
 // value is converted without float64 arithmetic; -0 and NaN come out as the
 // float64 sum gives them.
-template <typename UT, typename GT>
+template <typename UT, typename GT, bool kExact>
 __device__ __forceinline__ void buf_store_one_row(void* G, int64_t ldg, uint32_t u, int col, int64_t D,
                                                   const typename Cols<UT>::raw& r) {
     uint32_t f[kColsPerLane];   // fp32 bits per column
@@ -534,7 +721,7 @@ __device__ __forceinline__ void buf_store_one_row(void* G, int64_t ldg, uint32_t
         if constexpr (sizeof(GT) == 4) w[e] = f[e];
         else w[e] = f32_bits_to_bf16(f[2 * e]) | (f32_bits_to_bf16(f[2 * e + 1]) << 16);
     }
-    buf_store_words<GT>(G, ldg, u, col, D, w);
+    buf_store_words<GT, kExact>(G, ldg, u, col, D, w);
 }
 
 __device__ __forceinline__ void store_partial(double* row, int64_t col, int64_t D, const double (&x)[kColsPerLane]) {
@@ -564,11 +751,13 @@ __device__ __forceinline__ int64_t chunk_start(const SumParams& a, int64_t c, ui
 // ids (a segment per row or two, so the most stores and roundings per row)
 // and start first, while the long segments of the frequent ids, which only
 // stream rows, fill the slots that free up.
-// kExact (D a multiple of 4): the wavefront loads kRunRows rows at a time into
-// registers (lanes past D read column 0 and store nothing), then walks them in
-// order; a row that starts a segment resets the sum, a row that ends one
-// stores it.  Segment boundaries depend only on the sorted ids, so every branch
-// is uniform across the wavefront.  Otherwise one row at a time.
+// The wavefront loads kRunRows rows at a time into registers (lanes past D read
+// column 0 and store nothing; where D is not a multiple of 4 the lane that
+// holds a row's last columns reads its whole group, which lies inside one
+// 16-byte chunk of the row, and stores only the columns below D), then walks
+// them in order; a row that starts a segment resets the sum, a row that ends
+// one stores it.  Segment boundaries depend only on the sorted ids, so every
+// branch is uniform across the wavefront.
 template <typename UT, typename GT, bool kExact>
 __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
     using raw = typename Cols<UT>::raw;
@@ -593,90 +782,72 @@ __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
     // the chunk's first segment began earlier and ends here: list the chunk
     // for the launch that adds the pieces (once, from the first slab)
     bool ends_crossing = false;
-    if constexpr (kExact) {
-        const int64_t colc = col_ok ? col : 0;
-        // ids, positions and segment numbers of a batch, one per lane (lane nr
-        // holds the id after the batch, if any); read back per row with lane
-        // reads instead of a memory round trip per row.  The next batch's are
-        // loaded behind the current batch's rows.
-        auto batch_meta = [&](int64_t s0, uint32_t& kv, uint32_t& pv, uint32_t& uv) {
-            const int nr = (int)min((int64_t)kRunRows, k1 - s0);
-            const int64_t kl = s0 + min(lane, nr);
-            const bool in = s0 < k1;
-            kv = in && lane <= nr && kl < a.P ? a.K[kl] : 0xFFFFFFFFu;
-            pv = in && lane < nr ? a.pos[kl] : 0u;
-            uv = in && lane < nr ? a.uid[kl] : 0u;
-        };
-        uint32_t kv, pv, uv;
-        batch_meta(k0, kv, pv, uv);
-        uint32_t kprev = 0;   // id of the row before the batch (read only past the chunk's first row)
-        for (int64_t s0 = k0; s0 < k1; s0 += kRunRows) {
-            const int nr = (int)min((int64_t)kRunRows, k1 - s0);
-            raw rows[kRunRows];
+    const int64_t colc = col_ok ? col : 0;
+    // ids, positions and segment numbers of a batch, one per lane (lane nr
+    // holds the id after the batch, if any); read back per row with lane
+    // reads instead of a memory round trip per row.  The next batch's are
+    // loaded behind the current batch's rows.
+    auto batch_meta = [&](int64_t s0, uint32_t& kv, uint32_t& pv, uint32_t& uv) {
+        const int nr = (int)min((int64_t)kRunRows, k1 - s0);
+        const int64_t kl = s0 + min(lane, nr);
+        const bool in = s0 < k1;
+        kv = in && lane <= nr && kl < a.P ? a.K[kl] : 0xFFFFFFFFu;
+        pv = in && lane < nr ? a.pos[kl] : 0u;
+        uv = in && lane < nr ? a.uid[kl] : 0u;
+    };
+    uint32_t kv, pv, uv;
+    batch_meta(k0, kv, pv, uv);
+    uint32_t kprev = 0;   // id of the row before the batch (read only past the chunk's first row)
+    for (int64_t s0 = k0; s0 < k1; s0 += kRunRows) {
+        const int nr = (int)min((int64_t)kRunRows, k1 - s0);
+        raw rows[kRunRows];
 #pragma unroll
-            for (int r = 0; r < kRunRows; ++r) {
-                const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)pv, r < nr ? r : 0);
-                rows[r] = *reinterpret_cast<const raw*>(U + (int64_t)p * a.ldu + colc);
-            }
-            uint32_t kn, pn, un;
-            batch_meta(s0 + kRunRows, kn, pn, un);
-#pragma unroll
-            for (int r = 0; r < kRunRows; ++r) {
-                const int64_t k = s0 + r;
-                if (r < nr) {
-                    const uint32_t kr = (uint32_t)__builtin_amdgcn_readlane((int)kv, r);
-                    if (k > run0 && (r == 0 ? kprev != kr
-                                            : (uint32_t)__builtin_amdgcn_readlane((int)kv, r - 1) != kr)) {
-                        run0 = k;
-#pragma unroll
-                        for (int e = 0; e < kColsPerLane; ++e) acc[e] = 0.0;
-                    }
-                    double x[kColsPerLane];
-                    Cols<UT>::widen(rows[r], x);
-#pragma unroll
-                    for (int e = 0; e < kColsPerLane; ++e) acc[e] += x[e];
-                    const bool chunk_end = k + 1 == k1;
-                    if (chunk_end || (uint32_t)__builtin_amdgcn_readlane((int)kv, r + 1) != kr) {
-                        const bool first = run0 == k0 && began_before;
-                        const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)uv, r);
-                        if (first || (chunk_end && ends_after)) {
-                            store_partial((first ? a.partA : a.partB) + (int64_t)c * a.D, col, a.D, acc);
-                            ends_crossing |= first && !(chunk_end && ends_after);
-                        } else if (run0 == k) {
-                            buf_store_one_row<UT, GT>(a.G, a.ldg, u, (int)col, a.D, rows[r]);
-                        } else {
-                            buf_store_cols<GT>(a.G, a.ldg, u, (int)col, a.D, acc);
-                        }
-                    }
-                }
-            }
-            kprev = (uint32_t)__builtin_amdgcn_readlane((int)kv, kRunRows - 1);
-            kv = kn;
-            pv = pn;
-            uv = un;
+        for (int r = 0; r < kRunRows; ++r) {
+            const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)pv, r < nr ? r : 0);
+            rows[r] = *reinterpret_cast<const raw*>(U + (int64_t)p * a.ldu + colc);
         }
-    } else {
-        for (int64_t k = k0; k < k1; ++k) {
-            if (k > run0 && a.K[k] != a.K[k - 1]) {
-                run0 = k;
-                for (int e = 0; e < kColsPerLane; ++e) acc[e] = 0.0;
-            }
-            raw r;
-            load_cols<UT>(U + (int64_t)a.pos[k] * a.ldu, col, a.D, col_ok, r);
-            double x[kColsPerLane];
-            Cols<UT>::widen(r, x);
-            for (int e = 0; e < kColsPerLane; ++e) acc[e] += x[e];
-            const bool chunk_end = k + 1 == k1;
-            if (chunk_end || a.K[k + 1] != a.K[k]) {
+        uint32_t kn, pn, un;
+        batch_meta(s0 + kRunRows, kn, pn, un);
+#pragma unroll
+        for (int r = 0; r < kRunRows; ++r) {
+            const int64_t k = s0 + r;
+            if (r < nr) {
+                const uint32_t kr = (uint32_t)__builtin_amdgcn_readlane((int)kv, r);
+                if (k > run0 && (r == 0 ? kprev != kr
+                                        : (uint32_t)__builtin_amdgcn_readlane((int)kv, r - 1) != kr)) {
+                    run0 = k;
+#pragma unroll
+                    for (int e = 0; e < kColsPerLane; ++e) acc[e] = 0.0;
+                }
+                const bool chunk_end = k + 1 == k1;
+                const bool ends = chunk_end || (uint32_t)__builtin_amdgcn_readlane((int)kv, r + 1) != kr;
                 const bool first = run0 == k0 && began_before;
-                if (first || (chunk_end && ends_after)) {
-                    store_partial((first ? a.partA : a.partB) + (int64_t)c * a.D, col, a.D, acc);
-                    ends_crossing |= first && !(chunk_end && ends_after);
-                } else if (col_ok) {
-                    store_cols<GT>(a.G, a.ldg, a.uid[k], col, a.D, acc);
+                const bool piece = first || (chunk_end && ends_after);
+                if (ends && run0 == k && !piece) {
+                    // a segment of this row alone: no float64 arithmetic
+                    const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)uv, r);
+                    buf_store_one_row<UT, GT, kExact>(a.G, a.ldg, u, (int)col, a.D, rows[r]);
+                    continue;
+                }
+                double x[kColsPerLane];
+                Cols<UT>::widen(rows[r], x);
+#pragma unroll
+                for (int e = 0; e < kColsPerLane; ++e) acc[e] += x[e];
+                if (ends) {
+                    if (piece) {
+                        store_partial((first ? a.partA : a.partB) + (int64_t)c * a.D, col, a.D, acc);
+                        ends_crossing |= first && !(chunk_end && ends_after);
+                    } else {
+                        const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)uv, r);
+                        buf_store_cols<GT, kExact>(a.G, a.ldg, u, (int)col, a.D, acc);
+                    }
                 }
             }
         }
+        kprev = (uint32_t)__builtin_amdgcn_readlane((int)kv, kRunRows - 1);
+        kv = kn;
+        pv = pn;
+        uv = un;
     }
     // (a chunk that begins inside a segment begins at c L, so seg0 and start0
     // are that segment's number and start)
@@ -691,9 +862,10 @@ __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
 // segment ends), add the segment's pieces in chunk order: the start chunk's
 // last-segment partial, then the first-segment partials of the later chunks.
 // One column per lane, 64 columns per wavefront, kFixBatch partial rows loaded
-// at a time; the grid walks the (listed chunk, column slab) items.  The
+// at a time (kFixShort where no more are left); the grid walks the (listed chunk, column slab) items.  The
 // list order varies from run to run; each item's result does not.
-constexpr int kFixBatch = 64;
+constexpr int kFixBatch = 32;
+constexpr int kFixShort = 4;
 constexpr int kFixBlocks = 1024;
 
 template <typename GT>
@@ -712,17 +884,22 @@ __global__ __launch_bounds__(kCoalThreads) void coal_fixup(SumParams a) {
         const bool ok = col < a.D;
         const int64_t colc = ok ? col : 0;
         double acc = a.partB[(int64_t)c0 * a.D + colc];
-        for (int cc = c0 + 1; cc <= c; cc += kFixBatch) {
-            double x[kFixBatch];
+        auto add = [&](int cc, auto batch) {
+            constexpr int kBatch = decltype(batch)::value;
+            double x[kBatch];
 #pragma unroll
-            for (int q = 0; q < kFixBatch; ++q) {
+            for (int q = 0; q < kBatch; ++q) {
                 const int ccq = cc + q <= c ? cc + q : c;
                 x[q] = a.partA[(int64_t)ccq * a.D + colc];
             }
 #pragma unroll
-            for (int q = 0; q < kFixBatch; ++q)
+            for (int q = 0; q < kBatch; ++q)
                 if (cc + q <= c) acc += x[q];
-        }
+        };
+        // most segments cross one or two boundaries
+        int cc = c0 + 1;
+        for (; c - cc >= kFixShort; cc += kFixBatch) add(cc, std::integral_constant<int, kFixBatch>{});
+        if (cc <= c) add(cc, std::integral_constant<int, kFixShort>{});
         if (ok) {
             GT* row = static_cast<GT*>(a.G) + (int64_t)u * a.ldg;
             if constexpr (sizeof(GT) == 4) row[col] = (float)acc;
@@ -756,10 +933,21 @@ CoalPlan coal_plan(int64_t P, int64_t V, int64_t D) {
     int64_t maxc = kMaxPartialElems / (D > 0 ? D : 1);
     maxc = maxc < 1 ? 1 : (maxc > kMaxChunks ? kMaxChunks : maxc);
     int64_t m = (P + (int64_t)kRunRows * maxc - 1) / ((int64_t)kRunRows * maxc);
-    if (m < kMinChunkBatches) m = kMinChunkBatches;
+    c.nslabs = (int)((D + kSlabCols - 1) / kSlabCols);
+    // at least kMinChunkBatches batches, or as few as keep the wavefronts of a
+    // small batch within the resident ones and its chunks (the pieces of a
+    // long segment, which are added one after another) within kFewChunks
+    const int64_t slots = kSumWaveSlots / c.nslabs < kFewChunks ? kSumWaveSlots / c.nslabs : kFewChunks;
+    int64_t least = 1;
+    while (least < kMinChunkBatches && (P + kRunRows * least - 1) / (kRunRows * least) > slots) ++least;
+    if (m < least) m = least;
     c.L = (int64_t)kRunRows * m;
     c.nchunks = (int)((P + c.L - 1) / c.L);
-    c.nslabs = (int)((D + kSlabCols - 1) / kSlabCols);
+    // room for the chunks of every smaller batch too
+    const int64_t full = (P + kRunRows * kMinChunkBatches - 1) / (kRunRows * kMinChunkBatches);
+    const int64_t few = (P + kRunRows - 1) / kRunRows;
+    int64_t room = full < maxc ? full : maxc;
+    if ((few < slots ? few : slots) > room) room = few < slots ? few : slots;
     size_t off = 256;   // status words, shared layout with the step workspace
     const size_t nt = (size_t)(c.ntiles > 0 ? c.ntiles : 1);
     const size_t np = (size_t)(P > 0 ? P : 1);
@@ -774,7 +962,7 @@ CoalPlan coal_plan(int64_t P, int64_t V, int64_t D) {
     c.tileoff = off; off = align256(off + nt * 4);
     c.uid = off; off = align256(off + np * 4);
     c.seg_start = off; off = align256(off + (np + 1) * 4);
-    const size_t nc = (size_t)(c.nchunks > 0 ? c.nchunks : 1);
+    const size_t nc = (size_t)(room > 0 ? room : 1);
     c.part_a = off; off = align256(off + nc * (size_t)D * 8);
     c.part_b = off; off = align256(off + nc * (size_t)D * 8);
     c.fix_list = off; off = align256(off + nc * 16);
@@ -798,12 +986,44 @@ hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s) {
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws + c.hist);
     uint32_t* offs = reinterpret_cast<uint32_t*>(ws + c.offs);
     uint32_t* tile_bad = reinterpret_cast<uint32_t*>(ws + c.tile_bad);
-    const bool in_block = c.ntiles <= kInBlockOffsetTiles;
 
     // 1. sort
     const uint32_t* kin = nullptr;
     const uint32_t* vin = nullptr;
-    for (int q = 0; q < c.passes; ++q) {
+    // Counted places (see coal_rank) where that is cheaper than the radix sort.
+    const bool small = a.P <= kRankMaxTokens;
+    const int nrank = (int)((a.P + kWave - 1) / kWave);
+    if (small) {
+        const bool one = a.P <= kRankOneTile;
+        RankParams p;
+        p.tok = a.tok;
+        p.P = (int)a.P;
+        p.V = a.V;
+        p.tile = one ? (int)((a.P + kRankThreads - 1) / kRankThreads) * kRankThreads : kRankTile;
+        p.bits = bits_for(a.V);
+        p.keys_out = ka;
+        p.vals_out = va;
+        p.blk_bad = hist;    // the digit counts are not used here
+        switch (p.tile / kRankThreads) {
+        case 1: coal_rank<1><<<nrank, kRankThreads, 0, s>>>(p); break;
+        case 2: coal_rank<2><<<nrank, kRankThreads, 0, s>>>(p); break;
+        case 3: coal_rank<3><<<nrank, kRankThreads, 0, s>>>(p); break;
+        default: coal_rank<4><<<nrank, kRankThreads, 0, s>>>(p); break;
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        kin = ka;
+        vin = va;
+        if (!one) {
+            coal_merge<<<nrank, kMergeThreads, 0, s>>>(MergeParams{ka, va, kb, vb, (int)a.P,
+                                                                   (int)((a.P + kRankTile - 1) / kRankTile)});
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            kin = kb;
+            vin = vb;
+        }
+    }
+    for (int q = 0; !small && q < c.passes; ++q) {
         SortPass p;
         p.tok = q == 0 ? a.tok : nullptr;
         p.keys_in = kin;
@@ -816,16 +1036,14 @@ hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s) {
         p.bits = c.digit_bits;
         p.ntiles = c.ntiles;
         p.hist = hist;
-        p.offs = in_block ? nullptr : offs;
+        p.offs = offs;
         p.tile_bad = tile_bad;
         coal_hist<<<c.ntiles, kCoalThreads, 0, s>>>(p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (!in_block) {
-            coal_scan<<<1, 1024, 0, s>>>(hist, offs, (int64_t)c.ntiles << p.bits);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
+        coal_scan<<<1, 1024, 0, s>>>(hist, offs, (int64_t)c.ntiles << p.bits);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
         coal_scatter<<<c.ntiles, kCoalThreads, 0, s>>>(p);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -839,25 +1057,30 @@ hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s) {
     h.P = a.P;
     h.ntiles = c.ntiles;
     h.tilecnt = reinterpret_cast<uint32_t*>(ws + c.tilecnt);
-    h.tileoff = in_block ? nullptr : reinterpret_cast<uint32_t*>(ws + c.tileoff);
+    h.tileoff = reinterpret_cast<uint32_t*>(ws + c.tileoff);
     h.uid = reinterpret_cast<uint32_t*>(ws + c.uid);
     h.seg_start = reinterpret_cast<uint32_t*>(ws + c.seg_start);
     h.idx = a.idx;
     h.n_out = a.n_out;
     h.fix_count = reinterpret_cast<uint32_t*>(ws + c.fix_count);
-    h.tile_bad = tile_bad;
+    h.tile_bad = small ? hist : tile_bad;
     h.status = status;
-    coal_heads_count<<<c.ntiles, kCoalThreads, 0, s>>>(h);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (!in_block) {
+    hipError_t e = hipSuccess;
+    if (small) {
+        coal_heads_small<<<(unsigned)((a.P + kHeadThreads - 1) / kHeadThreads), kHeadThreads, 0, s>>>(h, nrank);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    } else {
+        coal_heads_count<<<c.ntiles, kCoalThreads, 0, s>>>(h);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
         coal_scan<<<1, 1024, 0, s>>>(h.tilecnt, reinterpret_cast<uint32_t*>(ws + c.tileoff), c.ntiles);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
+        coal_heads_write<<<c.ntiles, kCoalThreads, 0, s>>>(h);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    coal_heads_write<<<c.ntiles, kCoalThreads, 0, s>>>(h);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
 
     // 3. sums
     SumParams m;
