@@ -16,15 +16,25 @@
 // Tiling: one block computes a 256 x 256 tile of G (256 rows of the
 // vocabulary, 256 hidden columns) with 8 wavefronts, two per SIMD, so one
 // wave's MFMAs run while the other waits on LDS or a barrier; wave w owns the
-// 64 x 128 part (w % 4, w / 4) as 2 x 4 MFMA 32x32x16 tiles (a 4-wave form
-// with 128 x 128 parts is a compile-time option).  The contraction runs over
-// the tokens in steps of 64.  Both operands are stored token-major, so each
-// step's 64 x 256 slices go from global memory straight into LDS as they are
+// 64 x 128 part (w % 4, w / 4) as 2 x 4 MFMA 32x32x16 tiles.  The contraction
+// runs over the tokens in steps of 32.  Both operands are stored token-major, so
+// each step's 32 x 256 slices go from global memory straight into LDS as they are
 // (16-byte buffer loads with an LDS destination) and are turned into the MFMA
 // operand layout (8 consecutive tokens per lane) by the LDS transpose read
-// ds_read_b64_tr_b16.  A ring of LDS stages keeps the loads of the next
-// step(s) in flight while a step is multiplied, and the operand reads of
-// each 16-token sub-step run in the shadow of the previous sub-step's MFMAs.
+// ds_read_b64_tr_b16.  A ring of four LDS stages keeps the loads of the next
+// three steps in flight while a step is multiplied; the operands of each
+// 16-token sub-step are read behind the previous sub-step's MFMAs, across the
+// step barrier too, so no MFMA waits for an LDS read it follows directly.
+//
+// What bounds it: operand delivery and power.  At 128256 x 4096 x 16384 (bf16,
+// normal data) the kernel takes 13.45 ms, 1280 TFLOP/s, with the chip clocked
+// down to ~1.65 GHz; with all-zero operands the same launch (two 64-token
+// stages) takes 11.7 ms at 2.38 GHz, without its operand loads 7.6 ms, and with
+// the loads and LDS reads but no MFMA 11.5 ms.  Before the operand reads
+// crossed the barrier: 14.5 ms.  Barrier crossing with two 64-token stages:
+// 13.7 ms; five 32-token stages 1% slower than four; 4 waves of 128 x 128
+// parts, which read a third less LDS, 15.3 ms (one wave per SIMD leaves the
+// barrier uncovered).
 // Tiles are numbered so that the blocks one XCD runs at a time share a few
 // row tiles and a window of column tiles (its L2 holds their slices).
 
@@ -40,8 +50,11 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
 constexpr int kGemmWaves = 8;                   // wavefronts per block
@@ -51,8 +64,16 @@ constexpr int kWavesM = kGemmWaves / kWavesN;
 constexpr int kBM = kLmheadTile;        // rows of G per block (vocabulary)
 constexpr int kBN = kLmheadTile;        // columns of G per block (hidden)
 constexpr int kBK = kLmheadK;           // tokens per step
-constexpr int kStages = 2;                      // LDS stages (steps in flight)
-constexpr int kGroupM = 2;                      // row tiles per group of the tile order
+constexpr int kStages = 4;                      // LDS stages (steps in flight)
+// Row tiles per group of the tile order: the 32 tiles an XCD runs at a time
+// are 2 x 16 (long contractions) or 8 x 4 of row by column tiles.  8 x 4 reads
+// 12 operand slices per step instead of 18 (V x 4096 x T, us, groups of 2 / 4 /
+// 8: 32000 x 2048 530 / 510 / 501, 128256 x 2048 1902 / 1876 / 1870); over a
+// long contraction the tiles drift apart and the wide groups lose
+// (128256 x 16384: 13450 / 13540 / 14250; x 8192: 7040 / 7040 / 7310; x 4096:
+// 3610 / 3570 / 3605).
+constexpr int kGroupMShort = 8, kGroupMLong = 2;
+constexpr int64_t kGroupShortT = 4096;          // longest contraction of the wide groups
 constexpr int kRowBytes = kBM * 2;              // one token's 256 bf16 of one operand
 constexpr int kOperandBytes = kBK * kRowBytes;  // one operand's slice of a step
 constexpr int kStageBytes = 2 * kOperandBytes;  // dY slice, then H slice
@@ -62,6 +83,7 @@ constexpr int kWaveRows = kBM / kWavesM;        // rows of one wave's part of th
 constexpr int kWaveCols = kBN / kWavesN;        // its columns (128)
 constexpr int kMT = kWaveRows / 32;             // 32 x 32 MFMA tiles per wave: kMT x kNT
 constexpr int kNT = kWaveCols / 32;
+constexpr int kSub = kBK / 16;                  // 16-token sub-steps of a step
 constexpr int kXcds = 8;
 constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit data format, gfx9 family
 
@@ -70,8 +92,9 @@ static_assert(kBM == 256 && kBK % 16 == 0, "wave tiling assumes 256 x 256 tiles"
 static_assert(kGemmWaves == 8, "8 wavefronts per block");
 static_assert(kStages >= 2 && kLoadsPerWave * kRowsPerLoad * kGemmWaves == kBK, "load split");
 static_assert(kStages * kStageBytes <= 160 * 1024, "LDS of one CU");
-static_assert((kStages - 2) * 2 * kLoadsPerWave < 64, "vmcnt range");
-static_assert(kStages == 2, "a ring of two stages");
+static_assert(2 * kLoadsPerWave <= kMT * kNT, "at most one load behind each MFMA of a sub-step");
+static_assert(kSub % 2 == 0, "a step ends on the register set it began with");
+static_assert(kStages <= 5, "the step loop is written out for at most five stages");
 
 struct Params {
     const uint16_t* dY;   // [T][ldy] bf16
@@ -93,18 +116,31 @@ struct Params {
     int group_m;          // row tiles per group of the tile order
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, int64_t bytes) {
-    const int n = bytes > 0x7FFFFFF0 ? 0x7FFFFFF0 : (int)bytes;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, n, kBufferWord3);
+// Raw buffer resource of `bytes` bytes at a wave-uniform base, as the four
+// words the load takes (readfirstlane keeps them in scalar registers).
+__device__ __forceinline__ i32x4 rsrc(const void* base, int64_t bytes) {
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
+    i32x4 r;
+    r.x = __builtin_amdgcn_readfirstlane((int)p);
+    r.y = __builtin_amdgcn_readfirstlane((int)(p >> 32) & 0xFFFF);
+    r.z = __builtin_amdgcn_readfirstlane(bytes > 0x7FFFFFF0 ? 0x7FFFFFF0 : (int)bytes);
+    r.w = kBufferWord3;
+    return r;
 }
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
 
-// fp32 -> bf16, round to nearest even (NaN stays NaN).
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float x) {
-    const uint32_t u = __float_as_uint(x);
-    const uint32_t rne = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-    return (x != x) ? ((u >> 16) | 0x0040u) : rne;
+// Two fp32 -> bf16 (low, high half), round to nearest even: one v_cvt_pk_bf16_f32.
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
+    const f32x2 f = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+}
+
+// Orders a wave's LDS accesses before and after it (a wave's LDS operations
+// execute in order, so only the compiler has to be held).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // Logical tile -> (row tile, column tile): groups of group_m row tiles, row
@@ -136,7 +172,8 @@ template <typename GT>
 constexpr int kStripBytes = kStripRows<GT> * kStripPitch<GT>;
 constexpr int kRedBytes = (kWavesN + kWavesM) * kLmheadTile * 4;   // row and column partials
 
-template <typename GT>
+// kFull: the whole tile lies inside the table (no element is checked).
+template <typename GT, bool kFull>
 __device__ __forceinline__ void epilogue(const Params& a, int tm, int tn, f32x16 (&acc)[kMT][kNT], uint8_t* strip,
                                          uint8_t* red) {
     constexpr int kEs = (int)sizeof(GT);
@@ -174,24 +211,30 @@ __device__ __forceinline__ void epilogue(const Params& a, int tm, int tn, f32x16
             for (int nt = 0; nt < kNT; ++nt) {
                 const bool nv = n0 + nt * 32 + col < a.D;
 #pragma unroll
-                for (int ii = 0; ii < kRegsPerStrip; ++ii) {
+                for (int ii = 0; ii < kRegsPerStrip; ii += 2) {
+                    // registers i and i + 1 hold rows r and r + 1
                     const int i = sp * kRegsPerStrip + ii;
                     const int r = 8 * (i >> 2) + 4 * half + (i & 3) - sp * kRows;
-                    const bool v = nv && mstrip + r < a.V;
-                    float g;
+                    float g0 = acc[mt][nt][i], g1 = acc[mt][nt][i + 1];
                     uint8_t* e = strip + r * kPitch + (nt * 32 + col) * kEs;
                     if constexpr (kEs == 2) {
-                        const uint32_t h = f32_to_bf16_bits(acc[mt][nt][i]);
+                        const uint32_t h = pack_bf16x2(g0, g1);
                         *reinterpret_cast<uint16_t*>(e) = (uint16_t)h;
-                        g = bf16_bits_to_f32(h);
+                        *reinterpret_cast<uint16_t*>(e + kPitch) = (uint16_t)(h >> 16);
+                        g0 = bf16_bits_to_f32(h & 0xFFFFu);
+                        g1 = __uint_as_float(h & 0xFFFF0000u);
                     } else {
-                        g = acc[mt][nt][i];
-                        *reinterpret_cast<float*>(e) = g;
+                        *reinterpret_cast<float*>(e) = g0;
+                        *reinterpret_cast<float*>(e + kPitch) = g1;
                     }
-                    cs[nt] += v ? g * g : 0.0f;
+                    // rows and columns past the table hold products of other data
+                    const bool v0 = kFull || (nv && mstrip + r < a.V);
+                    const bool v1 = kFull || (nv && mstrip + r + 1 < a.V);
+                    cs[nt] += v0 ? g0 * g0 : 0.0f;
+                    cs[nt] += v1 ? g1 * g1 : 0.0f;
                 }
             }
-            __syncthreads();
+            wave_lds_order();
             // read back, store, row sums
 #pragma unroll
             for (int pass = 0; pass < kRows / kRowsPerPass; ++pass) {
@@ -204,16 +247,16 @@ __device__ __forceinline__ void epilogue(const Params& a, int tm, int tn, f32x16
                 for (int q = 0; q < 4; ++q) {
                     if constexpr (kEs == 2) {
                         const float lo = bf16_bits_to_f32(w[q] & 0xFFFFu), hi = bf16_bits_to_f32(w[q] >> 16);
-                        rsum += n + 2 * q < a.D ? lo * lo : 0.0f;
-                        rsum += n + 2 * q + 1 < a.D ? hi * hi : 0.0f;
+                        rsum += kFull || n + 2 * q < a.D ? lo * lo : 0.0f;
+                        rsum += kFull || n + 2 * q + 1 < a.D ? hi * hi : 0.0f;
                     } else {
                         const float x = __uint_as_float(w[q]);
-                        rsum += n + q < a.D ? x * x : 0.0f;
+                        rsum += kFull || n + q < a.D ? x * x : 0.0f;
                     }
                 }
-                if (m < a.V) {
+                if (kFull || m < a.V) {
                     char* grow = static_cast<char*>(a.G) + (m * a.ldg + n) * kEs;
-                    if (n + kEpc <= a.D) {
+                    if (kFull || n + kEpc <= a.D) {
                         *reinterpret_cast<u32x4*>(grow) = w;
                     } else {
                         for (int e = 0; e < kEpc && n + e < a.D; ++e) {
@@ -228,7 +271,7 @@ __device__ __forceinline__ void epilogue(const Params& a, int tm, int tn, f32x16
                 for (int x = 1; x < kLanesPerRow; x <<= 1) rsum += __shfl_xor(rsum, x);
                 if (rb_chunk == 0) rows_lds[wn * kBM + wm * kWaveRows + mt * 32 + sp * kRows + r] = rsum;
             }
-            __syncthreads();   // the strip is rewritten next
+            wave_lds_order();   // the strip is rewritten next
         }
     }
     // columns: rows of the low lane half, then of the high half
@@ -258,9 +301,8 @@ __device__ __forceinline__ void epilogue(const Params& a, int tm, int tn, f32x16
 // explicitly with wait_vmcnt and a barrier before a stage is read.  M0 holds
 // the LDS base (wave-uniform) for the load and is restored afterwards; one
 // wait state separates its write from the load.
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rs, const void* lds_base, int voffset) {
-    const uint32_t base = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds_base);
+__device__ __forceinline__ void load_to_lds(i32x4 rs, uint32_t lds_base, int voffset) {
+    const uint32_t base = __builtin_amdgcn_readfirstlane(lds_base);
     uint32_t saved;
     asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
@@ -278,24 +320,30 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// The step barrier: at most N of this wave's vector-memory loads outstanding
+// (the next step's data has arrived), all of its LDS reads returned, then the
+// block's waves meet.  Written out because __syncthreads would also wait for
+// the loads that are to stay in flight.
+template <int N>
+__device__ __forceinline__ void wait_step() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 template <typename GT>
 __global__ __launch_bounds__(kThreads) void ember_lmhead_grad(Params a) {
-    // kStages ring of (dY slice, H slice) of kBK tokens each, one LDS array
-    // per stage, addressed statically (the step loop is unrolled by the ring
-    // size; with the compiler's load builtin this also lets it tell the stage
-    // being loaded from the stage being read).  Each slice
-    // row (one token, 256 columns, 512 bytes) is stored unpadded, its 16-byte
-    // chunks XOR-permuted by the row: chunk c of token row k sits at position
-    // c ^ (4 (k % 4)).  The transpose reads of a quarter-wave then cover all
-    // LDS banks once (no conflicts), and every wave-wide load still fills two
-    // whole rows, as the LDS-direct load requires (lane l -> base + 16 l).
-    __shared__ __attribute__((aligned(1024))) uint8_t lds0[kStageBytes];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds1[kStageBytes];
-    auto stage = [&](auto sc) -> uint8_t* {
-        constexpr int k = decltype(sc)::value;
-        if constexpr (k == 0) return lds0;
-        else return lds1;
-    };
+    // kStages stages of (dY slice, H slice) of kBK tokens each, addressed by their
+    // LDS byte offset.  Each slice row (one token, 256 columns, 512 bytes) is
+    // stored unpadded, its 16-byte chunks XOR-permuted by the row: chunk c of
+    // token row k sits at position c ^ (4 (k % 4)).  The transpose reads of a
+    // quarter-wave then cover all LDS banks once (no conflicts), and every
+    // wave-wide load still fills two whole rows, as the LDS-direct load
+    // requires (lane l -> base + 16 l).
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[kStages * kStageBytes];
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)lds;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = tid / kWave;
@@ -306,7 +354,7 @@ __global__ __launch_bounds__(kThreads) void ember_lmhead_grad(Params a) {
     // tiles of this launch's range
     const int64_t l = a.tile0 + (int64_t)(blockIdx.x % kXcds) * a.per_xcd + blockIdx.x / kXcds;
     if (l >= a.tile1) return;
-    const int64_t nk = (a.T + kBK - 1) / kBK;
+    const int nk = __builtin_amdgcn_readfirstlane((int)((a.T + kBK - 1) / kBK));   // T <= 2^30
     int tm, tn;
     tile_of(a, l, tm, tn);
     const int64_t v0 = (int64_t)tm * kBM;
@@ -322,19 +370,25 @@ __global__ __launch_bounds__(kThreads) void ember_lmhead_grad(Params a) {
         off_y[i] = (int)((row * a.ldy + chunk * 8) * 2);
         off_h[i] = (int)((row * a.ldh + chunk * 8) * 2);
     }
-    auto issue = [&](int64_t kt, uint8_t* st) {
-        // past the last step the resources cover no bytes: the loads write
-        // zeros into a stage that is not read again
+    // operand resources of step kt; past the last step they cover no bytes: the
+    // loads write zeros into a stage whose products are then exact zeros
+    struct StepLoads {
+        i32x4 ra, rb;
+    };
+    auto loads_of = [&](int kt) {
         const bool in = kt < nk;
-        const int64_t k0 = in ? kt * kBK : 0;
-        const __amdgpu_buffer_rsrc_t ra = rsrc(a.dY + k0 * a.ldy + v0, in ? ((a.T - k0) * a.ldy - v0) * 2 : 0);
-        const __amdgpu_buffer_rsrc_t rb = rsrc(a.H + k0 * a.ldh + d0, in ? ((a.T - k0) * a.ldh - d0) * 2 : 0);
-#pragma unroll
-        for (int i = 0; i < kLoadsPerWave; ++i) {
-            uint8_t* dst = st + (wave + kGemmWaves * i) * (kRowsPerLoad * kRowBytes);
-            load_to_lds(ra, dst, off_y[i]);
-            load_to_lds(rb, dst + kOperandBytes, off_h[i]);
-        }
+        const int64_t k0 = in ? (int64_t)kt * kBK : 0;
+        StepLoads sl;
+        sl.ra = rsrc(a.dY + k0 * a.ldy + v0, in ? ((a.T - k0) * a.ldy - v0) * 2 : 0);
+        sl.rb = rsrc(a.H + k0 * a.ldh + d0, in ? ((a.T - k0) * a.ldh - d0) * 2 : 0);
+        return sl;
+    };
+    // load j of this wave's 2 kLoadsPerWave loads of a step
+    auto issue_one = [&](const StepLoads& sl, uint32_t st, int j) {
+        const int i = j >> 1;
+        const uint32_t dst = st + (wave + kGemmWaves * i) * (kRowsPerLoad * kRowBytes);
+        if ((j & 1) == 0) load_to_lds(sl.ra, dst, off_y[i]);
+        else load_to_lds(sl.rb, dst + kOperandBytes, off_h[i]);
     };
 
     // transpose reads: lane l reads token row 8 (l / 32) + (l % 16) / 4 (+ 4),
@@ -354,22 +408,19 @@ __global__ __launch_bounds__(kThreads) void ember_lmhead_grad(Params a) {
         const int chunk = wn * (kWaveCols / 8) + t * 4 + cpart;
         tr_b[t] = tr_row * kRowBytes + (chunk ^ (4 * (tr_row & 3))) * 16 + 8 * (lane & 1) + kOperandBytes;
     }
-    auto rd = [&](const uint8_t* p) {
-        return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p);
+    auto rd = [&](uint32_t p) {
+        return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)p);
     };
-    auto frags = [&](const uint8_t* st, int kk, bf16x8 (&af)[kMT], bf16x8 (&bfr)[kNT]) {
-#pragma unroll
-        for (int t = 0; t < kMT; ++t) {
-            const uint8_t* pa = st + tr_a[t] + kk * 16 * kRowBytes;
-            af[t] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(rd(pa), rd(pa + 4 * kRowBytes),
-                                                                      0, 1, 2, 3, 4, 5, 6, 7));
-        }
-#pragma unroll
-        for (int t = 0; t < kNT; ++t) {
-            const uint8_t* pb = st + tr_b[t] + kk * 16 * kRowBytes;
-            bfr[t] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(rd(pb), rd(pb + 4 * kRowBytes),
-                                                                       0, 1, 2, 3, 4, 5, 6, 7));
-        }
+    // operand f of a 16-token sub-step, in the order the MFMAs first use them:
+    // A 0, B 0 .. kNT - 1, A 1 .. kMT - 1
+    auto frag = [&](uint32_t st, int kk, int f, bf16x8 (&af)[kMT], bf16x8 (&bfr)[kNT]) {
+        const bool is_b = f >= 1 && f <= kNT;
+        const int t = f == 0 ? 0 : is_b ? f - 1 : f - kNT;
+        const uint32_t p = st + (is_b ? tr_b[t] : tr_a[t]) + kk * 16 * kRowBytes;
+        const bf16x8 x = __builtin_bit_cast(bf16x8, __builtin_shufflevector(rd(p), rd(p + 4 * kRowBytes),
+                                                                            0, 1, 2, 3, 4, 5, 6, 7));
+        if (is_b) bfr[t] = x;
+        else af[t] = x;
     };
 
     f32x16 acc[kMT][kNT];
@@ -380,73 +431,67 @@ __global__ __launch_bounds__(kThreads) void ember_lmhead_grad(Params a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.0f;
 
-    // step kt (stage kt % kStages): this wave's loads of step kt are done
-    // once at most the later steps' are outstanding; the barrier makes every
-    // wave's visible and frees the stage of step kt - 1, which then takes the
-    // loads of step kt + kStages - 1
-    auto step = [&](int64_t kt, auto sc) {
+    // Step kt multiplies stage kt % 2 in four 16-token sub-steps.  While the
+    // MFMAs of a sub-step run, the operands of the next one are read into the
+    // other register set, one operand behind each MFMA (without the fences the
+    // scheduler fetches every operand just before its MFMA and waits for it).
+    // The block barrier sits before the last sub-step, whose operands are in
+    // registers by then: past it every wave has read all of stage kt % 2 and
+    // step kt + 1 lies in the other stage, so the last sub-step's MFMAs cover
+    // both the first operand reads of step kt + 1 and the loads of step
+    // kt + 2 into the freed stage, which have a whole step to arrive.
+    bf16x8 af[2][kMT], bfr[2][kNT];
+    auto step = [&](int kt, auto sc) {
         constexpr int k = decltype(sc)::value;
-        wait_vmcnt<(kStages - 2) * 2 * kLoadsPerWave>();
-        __syncthreads();
-        // the first sub-step's operand reads go out first, the loads of step
-        // kt + kStages - 1 behind them (the loads' inline assembly is a
-        // compiler memory barrier, so this order holds): the read latency
-        // overlaps the load issue, and the loads still have the whole step
-        const uint8_t* st = stage(sc);
-        bf16x8 af[2][kMT], bfr[2][kNT];
-        frags(st, 0, af[0], bfr[0]);
-        issue(kt + kStages - 1, stage(std::integral_constant<int, (k + kStages - 1) % kStages>{}));
-        // scheduling fences between sub-steps: the MFMAs of sub-step kk use
-        // operands read in an earlier region, and the reads of sub-step kk + 1
-        // fill their shadow (without the fences the scheduler fetches every
-        // operand just before its MFMA and waits for it)
-        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t st = lds_base + k * kStageBytes, next = lds_base + (k + 1) % kStages * kStageBytes;
+        const StepLoads sl = loads_of(kt + kStages);
 #pragma unroll
-        for (int kk = 0; kk < kBK / 16; ++kk) {
+        for (int kk = 0; kk < kSub; ++kk) {
             const int cur = kk & 1;
-            if (kk + 1 < kBK / 16) frags(st, kk + 1, af[cur ^ 1], bfr[cur ^ 1]);
-#pragma unroll
-            for (int mt = 0; mt < kMT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < kNT; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][mt], bfr[cur][nt], acc[mt][nt],
-                                                                          0, 0, 0);
-            // each MFMA followed by its share of the next sub-step's transpose reads
-            if (kk + 1 < kBK / 16) {
-                constexpr int kM = kMT * kNT, kR = 2 * (kMT + kNT);
-                constexpr int kRpm = (kR + kM - 1) / kM;   // reads after each MFMA
-#pragma unroll
-                for (int i = 0; i < kM; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-#pragma unroll
-                    for (int q = 0; q < kRpm; ++q)
-                        if (i * kRpm + q < kR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                }
-            }
+            const bool last = kk == kSub - 1;
+            if (last) wait_step<(kStages - 2) * 2 * kLoadsPerWave>();
             __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < kMT * kNT; ++i) {
+                const int mt = i / kNT, nt = i % kNT;
+                acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][mt], bfr[cur][nt], acc[mt][nt], 0, 0, 0);
+                if (i < kMT + kNT) {
+                    if (last) frag(next, 0, i, af[cur ^ 1], bfr[cur ^ 1]);
+                    else frag(st, kk + 1, i, af[cur ^ 1], bfr[cur ^ 1]);
+                }
+                if (last && i < 2 * kLoadsPerWave) issue_one(sl, st, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     };
-    // step 0 before the loop; step 1 is issued by step 0
-    issue(0, lds0);
+    // the first kStages steps go out before the loop, then the first operands
+    // are read once step 0 has arrived
+#pragma unroll
+    for (int q = 0; q < kStages; ++q) {
+        const StepLoads sl = loads_of(q);
+#pragma unroll
+        for (int j = 0; j < 2 * kLoadsPerWave; ++j) issue_one(sl, lds_base + q * kStageBytes, j);
+    }
+    wait_step<(kStages - 1) * 2 * kLoadsPerWave>();
+#pragma unroll
+    for (int f = 0; f < kMT + kNT; ++f) frag(lds_base, 0, f, af[0], bfr[0]);
     // whole rounds of kStages steps (one loop exit keeps the accumulators in
-    // place); the up to kStages - 1 steps past the last one multiply the zeros
-    // their loads wrote, which adds exact zeros
-    for (int64_t kt = 0; kt < nk; kt += kStages) {
+    // place); a step past the last one multiplies the zeros its loads wrote
+    for (int kt = 0; kt < nk; kt += kStages) {
         step(kt, std::integral_constant<int, 0>{});
         step(kt + 1, std::integral_constant<int, 1>{});
+        if constexpr (kStages > 2) step(kt + 2, std::integral_constant<int, 2>{});
+        if constexpr (kStages > 3) step(kt + 3, std::integral_constant<int, 3>{});
+        if constexpr (kStages > 4) step(kt + 4, std::integral_constant<int, 4>{});
     }
     wait_vmcnt<0>();   // the zero-filling loads past the end, before the LDS is reused
-    // epilogue scratch: wave w's strip in stage array w % kStages (after the
-    // strips of the lower waves there), the block's partial sums after the
-    // strips in lds1
+    // epilogue scratch: the waves' strips, then the block's partial sums
     constexpr int kStrip = kStripBytes<GT>;
-    constexpr int kStripsPerArray = (kGemmWaves + kStages - 1) / kStages;
-    static_assert(kStripsPerArray * kStrip + kRedBytes <= kStageBytes, "epilogue scratch fits the stages");
-    const int sarr = wave % kStages;
-    uint8_t* const sbase = sarr == 0 ? lds0 : lds1;
-    uint8_t* const strip = sbase + (wave / kStages) * kStrip;
-    uint8_t* const red = lds1 + kStripsPerArray * kStrip;
-    epilogue<GT>(a, tm, tn, acc, strip, red);
+    static_assert(kGemmWaves * kStrip + kRedBytes <= kStages * kStageBytes, "epilogue scratch fits the stages");
+    uint8_t* const strip = lds + wave * kStrip;
+    uint8_t* const red = lds + kGemmWaves * kStrip;
+    if (v0 + kBM <= a.V && d0 + kBN <= a.D) epilogue<GT, true>(a, tm, tn, acc, strip, red);
+    else epilogue<GT, false>(a, tm, tn, acc, strip, red);
 }
 
 } // namespace
@@ -474,7 +519,7 @@ hipError_t launch_lmhead_grad(const LmheadArgs& x, hipStream_t s) {
     p.P = x.P;
     p.MT = pl.MT;
     p.NT = pl.NT;
-    p.group_m = kGroupM;
+    p.group_m = x.T <= kGroupShortT ? kGroupMShort : kGroupMLong;
     const int64_t total = (int64_t)pl.MT * pl.NT;
     const int64_t per_launch = kMaxGridBlocks;   // a multiple of kXcds
     for (int64_t t0 = 0; t0 < total; t0 += per_launch) {
