@@ -116,14 +116,15 @@ def _dtype(t: torch.Tensor) -> int:
 
 
 def _ld(t: torch.Tensor) -> int:
-    if t.dim() != 2 or (t.size(1) > 1 and t.stride(1) != 1):
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2 or (shape[1] > 1 and stride[1] != 1):
         raise TypeError("a 2-D tensor with unit column stride is required")
-    if t.size(0) > 1:
-        return t.stride(0)
+    if shape[0] > 1:
+        return stride[0]
     # one row: the stride is never used to address a second row; give the
     # smallest one that keeps the library's 16-byte row rule
     q = max(1, 16 // t.element_size())
-    return (t.size(1) + q - 1) // q * q
+    return (shape[1] + q - 1) // q * q
 
 
 def _ptr(t):
@@ -131,7 +132,11 @@ def _ptr(t):
 
 
 def _stream(t: torch.Tensor):
-    return torch.cuda.current_stream(t.device).cuda_stream
+    """Handle of the current stream of t's device.  The raw query takes 0.2 us;
+    making a Stream object for it takes 1.9 us of a small step's ~15."""
+    if not t.is_cuda:
+        return torch.cuda.current_stream(t.device).cuda_stream   # refuses a host tensor
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def _check(status: int, where: str) -> None:
