@@ -74,6 +74,13 @@ constexpr int kStages = 4;                      // LDS stages (steps in flight)
 // 3610 / 3570 / 3605).
 constexpr int kGroupMShort = 8, kGroupMLong = 2;
 constexpr int64_t kGroupShortT = 4096;          // longest contraction of the wide groups
+// An fp32 G that does not fit the 256 MB last-level cache is stored
+// non-temporally: the apply pass would not find most of it there, and the
+// operands keep their place (whole step, us, cached / non-temporal: 32000 x 4096
+// x 2048 (524 MB) 779 / 754, 128256 x 2048 x 1024 (1.05 GB) 954 / 930).  One that
+// fits is left there for the apply pass (32000 x 1024 x 1024, 131 MB: 125 / 129).
+// bf16 G shows no difference at 65 MB to 1.05 GB.
+constexpr int64_t kStreamGBytes = (int64_t)256 << 20;
 constexpr int kRowBytes = kBM * 2;              // one token's 256 bf16 of one operand
 constexpr int kOperandBytes = kBK * kRowBytes;  // one operand's slice of a step
 constexpr int kStageBytes = 2 * kOperandBytes;  // dY slice, then H slice
@@ -114,6 +121,7 @@ struct Params {
     int64_t tile1;
     int64_t per_xcd;      // tiles per XCD: ceil((tile1 - tile0) / 8)
     int group_m;          // row tiles per group of the tile order
+    bool stream_g;        // fp32 G: non-temporal stores
 };
 
 // Raw buffer resource of `bytes` bytes at a wave-uniform base, as the four
@@ -257,7 +265,8 @@ __device__ __forceinline__ void epilogue(const Params& a, int tm, int tn, f32x16
                 if (kFull || m < a.V) {
                     char* grow = static_cast<char*>(a.G) + (m * a.ldg + n) * kEs;
                     if (kFull || n + kEpc <= a.D) {
-                        *reinterpret_cast<u32x4*>(grow) = w;
+                        if (kEs == 4 && a.stream_g) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(grow));
+                        else *reinterpret_cast<u32x4*>(grow) = w;
                     } else {
                         for (int e = 0; e < kEpc && n + e < a.D; ++e) {
                             if constexpr (kEs == 2)
@@ -520,6 +529,7 @@ hipError_t launch_lmhead_grad(const LmheadArgs& x, hipStream_t s) {
     p.MT = pl.MT;
     p.NT = pl.NT;
     p.group_m = x.T <= kGroupShortT ? kGroupMShort : kGroupMLong;
+    p.stream_g = x.g_dtype == 0 && x.V * x.D * 4 > kStreamGBytes;
     const int64_t total = (int64_t)pl.MT * pl.NT;
     const int64_t per_launch = kMaxGridBlocks;   // a multiple of kXcds
     for (int64_t t0 = 0; t0 < total; t0 += per_launch) {
