@@ -27,12 +27,12 @@
 // step barrier too, so no MFMA waits for an LDS read it follows directly.
 //
 // What bounds it: operand delivery and power.  At 128256 x 4096 x 16384 (bf16,
-// normal data) the kernel takes 13.45 ms, 1280 TFLOP/s, with the chip clocked
-// down to ~1.65 GHz; with all-zero operands the same launch (two 64-token
+// normal data) the kernel takes 13.5-14.6 ms by card, 1175-1275 TFLOP/s, with
+// the chip clocked down to ~1.65 GHz; with all-zero operands the same launch (two 64-token
 // stages) takes 11.7 ms at 2.38 GHz, without its operand loads 7.6 ms, and with
 // the loads and LDS reads but no MFMA 11.5 ms.  Before the operand reads
-// crossed the barrier: 14.5 ms.  Barrier crossing with two 64-token stages:
-// 13.7 ms; five 32-token stages 1% slower than four; 4 waves of 128 x 128
+// crossed the barrier: 14.5 ms where it now takes 13.5.  Barrier crossing with
+// two 64-token stages: 13.7 ms; five 32-token stages 1% slower than four; 4 waves of 128 x 128
 // parts, which read a third less LDS, 15.3 ms (one wave per SIMD leaves the
 // barrier uncovered).
 // Tiles are numbered so that the blocks one XCD runs at a time share a few
