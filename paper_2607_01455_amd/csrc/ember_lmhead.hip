@@ -63,7 +63,7 @@ constexpr int kWavesN = 2;                      // wave grid over the tile: kWav
 constexpr int kWavesM = kGemmWaves / kWavesN;
 constexpr int kBM = kLmheadTile;        // rows of G per block (vocabulary)
 constexpr int kBN = kLmheadTile;        // columns of G per block (hidden)
-constexpr int kBK = kLmheadK;           // tokens per step
+constexpr int kBK = kLmheadK / 2;       // tokens per step: half of the slice that 32-bit offsets allow for
 constexpr int kStages = 4;                      // LDS stages (steps in flight)
 // Row tiles per group of the tile order: the 32 tiles an XCD runs at a time
 // are 2 x 16 (long contractions) or 8 x 4 of row by column tiles.  8 x 4 reads
