@@ -287,6 +287,13 @@ struct RankParams {
 constexpr int kRankWaves = 16;
 constexpr int kRankThreads = kRankWaves * kWave;
 
+// Orders a wave's LDS accesses before and after it (a wave's LDS operations
+// execute in order, so only the compiler has to be held).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // One block per 64 positions; wavefront w compares them with the w-th of the
 // 16 runs of the tile (NQ groups of 64 ids each, staged in LDS and read back
 // four at a time by all lanes at once).  Bound by two vector operations per
@@ -295,7 +302,7 @@ constexpr int kRankThreads = kRankWaves * kWave;
 // scalar unit, which a compute unit has one of: 26 us at 16384 x 16384.)
 template <int NQ>
 __global__ __launch_bounds__(kRankThreads) void coal_rank(RankParams a) {
-    __shared__ uint32_t ids[kRankWaves][NQ * kWave];
+    __shared__ __attribute__((aligned(16))) uint32_t ids[kRankWaves][NQ * kWave];   // read as uint4
     __shared__ uint32_t cnt[kRankWaves][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -315,7 +322,8 @@ __global__ __launch_bounds__(kRankThreads) void coal_rank(RankParams a) {
         ids[wave][j * kWave + lane] = (g0 + j) * kWave + lane < a.P ? key_of_id(idq[j]) : kNoKey;
     const uint32_t kp = key_of_id(idp);
     const uint64_t any_bad = __ballot(p < a.P && (idp < 0 || idp >= a.V));
-    // the run is read by the wavefront that wrote it
+    // the run is read by the lanes of the wavefront that wrote it
+    wave_lds_order();
     uint32_t n = 0;
 #pragma unroll
     for (int j = 0; j < NQ; ++j) {
@@ -371,7 +379,7 @@ constexpr int kMergeThreads = kMergeWaves * kWave;
 constexpr int kMergeTiles = 8;      // tiles in LDS at a time: 64 KiB
 
 __global__ __launch_bounds__(kMergeThreads) void coal_merge(MergeParams a) {
-    __shared__ uint32_t ids[kMergeTiles * kRankTile];
+    __shared__ __attribute__((aligned(16))) uint32_t ids[kMergeTiles * kRankTile];   // filled as uint4
     __shared__ uint32_t cnt[kMergeWaves][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);

@@ -69,3 +69,84 @@ def test_workspace_covers_every_smaller_batch(D):
                    | {16 * k for k in (1, 511, 512, 513, 1024)} | {48 * 4096, 48 * 4096 + 1, 65536, 65537})
     got = [em.ember_coalesce_workspace_bytes(P, 50000, D) for P in sizes]
     assert all(a <= b for a, b in zip(got, got[1:]))
+
+
+# ---------------------------------------------------------------------------
+# the order in which the rows of one id are added
+# ---------------------------------------------------------------------------
+
+BIG = 2.0 ** 60     # float64: 2^60 + 1 rounds back to 2^60
+
+
+def ordered_batch(P, V, seed):
+    """Ids of three positions each: a third of them side by side, a third within
+    one run of 2048 positions, the rest anywhere in the batch.  Column j holds
+    the 1 in the id's row j and +-2^60 in the other two, so a sum is 1 only if
+    the row that was added last holds it: (0, 0, 1) in ascending order, and
+    something else whenever another row comes last."""
+    rng = np.random.default_rng(seed)
+    slot = np.full(P, -1, np.int64)
+    ids = 0
+
+    def take(pool):
+        nonlocal ids
+        for k in range(0, pool.size - 2, 3):
+            slot[pool[k:k + 3]] = ids
+            ids += 1
+
+    third = P // 3
+    near = np.arange(0, third)
+    take(near)
+    mid = np.arange(third, 2 * third)
+    for t in np.unique(mid // 2048):
+        take(rng.permutation(mid[mid // 2048 == t]))
+    take(rng.permutation(np.nonzero(slot < 0)[0]))
+    alone = np.nonzero(slot < 0)[0]
+    slot[alone] = ids + np.arange(alone.size)
+    tok = rng.choice(V, ids + alone.size, replace=False).astype(np.int64)[slot]
+    U = np.zeros((P, 4), np.float32)
+    for p_of in np.split(np.argsort(slot, kind="stable")[:3 * ids], ids):
+        p0, p1, p2 = np.sort(p_of)
+        U[p0, :3], U[p1, :3], U[p2, :3] = (1, BIG, BIG), (BIG, 1, -BIG), (-BIG, -BIG, 1)
+    U[:, 3] = rng.standard_normal(P)
+    return tok, U, ids
+
+
+def test_the_ordered_batch_tells_the_orders_apart():
+    tok, U, ids = ordered_batch(1025, 50021, 1)
+    triples = [np.nonzero(tok == t)[0] for t in np.unique(tok)]
+    triples = [p for p in triples if p.size == 3]
+    assert len(triples) == ids > 300
+
+    def add(rows):
+        s = np.zeros(3)
+        for r in rows:
+            s = s + U[r, :3].astype(np.float64)
+        return s.tolist()
+
+    for a, b, c in triples:
+        assert add((a, b, c)) == [0.0, 0.0, 1.0]
+        for other in ((a, c, b), (c, a, b), (b, c, a), (c, b, a)):   # every order with another row last
+            assert add(other) != [0.0, 0.0, 1.0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V", [70001, 2 ** 21 + 5])
+@pytest.mark.parametrize("P", [64, 1025, 2049, 4096, 4097, 16385, 65536, 65537])
+@pytest.mark.parametrize("D", [3, 4])
+def test_rows_of_an_id_are_added_in_position_order(P, D, V):
+    import oracle
+    tok, U, ids = ordered_batch(P, V, P)
+    U = np.ascontiguousarray(U[:, :D])
+    Ud = torch.zeros(P, 4, dtype=torch.float32, device=DEV)
+    Ud[:, :D] = torch.from_numpy(U).to(DEV)
+    co = em.Coalescer(P, V, D, dtype=torch.float32, device=DEV)
+    print(f"coalesce order P={P} D={D} V={V}", flush=True)
+    idx, G = co(torch.from_numpy(tok).to(DEV), Ud[:, :D])
+    st, idx_o, G_o = oracle.coalesce(tok, U, V)
+    assert st == oracle.OK and np.array_equal(idx.cpu().numpy(), idx_o)
+    G = G.cpu().numpy()
+    three = np.bincount(np.unique(tok, return_inverse=True)[1]) == 3
+    assert three.sum() == ids
+    assert np.array_equal(G[three, :3], np.tile(np.float32([0, 0, 1]), (ids, 1)))
+    assert np.array_equal(G.view(np.uint32), G_o.view(np.uint32))
