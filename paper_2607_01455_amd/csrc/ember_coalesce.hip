@@ -14,10 +14,10 @@
 // Pipeline (all integer work is exact and order-independent; every floating
 // point sum has a fixed order):
 //   1. stable sort of (id, position) pairs by id, so the positions of one id
-//      stay ascending: up to 65536 tokens by counting every place (coal_rank,
-//      and coal_merge past 4096), larger batches by an LSD radix sort, 1-4
-//      passes of up to 10 bits (digit histograms per tile, offsets, stable
-//      scatter ranked with wavefront ballots);
+//      stay ascending: most batches of up to 65536 tokens by counting every
+//      place (coal_rank, and coal_merge past 4096), the others (coal_counted)
+//      by an LSD radix sort, 1-4 passes of up to 10 bits (digit histograms per
+//      tile, offsets, stable scatter ranked with wavefront ballots);
 //   2. head flags of the sorted ids -> distinct ids, segment starts, and the
 //      segment number of every sorted entry;
 //   3. the sums: the sorted entries are cut into chunks of about L positions
@@ -50,7 +50,8 @@ constexpr int kCoalItems = 4;                        // keys per thread per tile
 constexpr int kTile = kCoalThreads * kCoalItems;     // keys per tile
 constexpr int kMaxDigitBits = 10;
 constexpr int kMaxBins = 1 << kMaxDigitBits;         // digits of up to 10 bits
-constexpr int64_t kRankMaxTokens = 65536;            // up to this many tokens: sorted by coal_rank
+constexpr int64_t kSmallTokens = 65536;              // up to this many tokens: 64 sort tiles, one heads
+                                                     // launch, and maybe places counted by coal_rank
 constexpr int64_t kRankOneTile = 4096;               // up to this many: in one tile
 constexpr int kRunRows = 16;                         // rows a wavefront holds at once
 constexpr int kMinChunkBatches = 3;                  // a chunk is at least this many batches
@@ -77,7 +78,7 @@ struct SortPass {
     int bits;
     int ntiles;
     uint32_t* hist;           // [bins][ntiles] digit counts per tile
-    const uint32_t* offs;     // [bins][ntiles] exclusive offsets
+    const uint32_t* offs;     // [bins][ntiles] exclusive offsets, or null (derived in the block)
     uint32_t* tile_bad;       // first pass: 1 where the tile holds an id outside [0, V)
 };
 
@@ -185,6 +186,7 @@ __global__ __launch_bounds__(kCoalThreads) void coal_scatter(SortPass a) {
     // [group][digit]: the group's count of the digit, then the count in the
     // earlier groups of the tile (< kTile, so 16 bits)
     __shared__ uint16_t cnt[kGroups * kMaxBins];
+    __shared__ uint32_t scan_lds[kCoalWaves];
     const int bins = 1 << a.bits;
     const int tile = blockIdx.x;
     const int t = threadIdx.x;
@@ -206,7 +208,37 @@ __global__ __launch_bounds__(kCoalThreads) void coal_scatter(SortPass a) {
         }
     }
 
-    for (int b = t; b < bins; b += kCoalThreads) off[b] = a.offs[(int64_t)b * a.ntiles + tile];
+    if (a.offs != nullptr) {
+        for (int b = t; b < bins; b += kCoalThreads) off[b] = a.offs[(int64_t)b * a.ntiles + tile];
+    } else {
+        // offset of digit b in this tile = keys of smaller digits in every tile
+        // + keys of digit b in earlier tiles; thread t owns digits
+        // [t * per, (t + 1) * per)
+        const int per = bins > kCoalThreads ? bins / kCoalThreads : 1;
+        uint32_t tot[kMaxBins / kCoalThreads], before[kMaxBins / kCoalThreads];
+        uint32_t mine = 0;
+        for (int q = 0; q < per; ++q) {
+            const int b = t * per + q;
+            tot[q] = 0;
+            before[q] = 0;
+            if (b < bins) {
+#pragma unroll 16
+                for (int k = 0; k < a.ntiles; ++k) {
+                    const uint32_t c = a.hist[(int64_t)b * a.ntiles + k];
+                    tot[q] += c;
+                    if (k < tile) before[q] += c;
+                }
+            }
+            mine += tot[q];
+        }
+        uint32_t all;
+        uint32_t excl = block_excl_scan(mine, scan_lds, &all);
+        for (int q = 0; q < per; ++q) {
+            const int b = t * per + q;
+            if (b < bins) off[b] = excl + before[q];
+            excl += tot[q];
+        }
+    }
     {
         // clear the counts, two 16-bit entries per word
         uint32_t* c32 = reinterpret_cast<uint32_t*>(cnt);
@@ -255,7 +287,7 @@ __global__ __launch_bounds__(kCoalThreads) void coal_scatter(SortPass a) {
 }
 
 // ---------------------------------------------------------------------------
-// the sort of batches of up to kRankMaxTokens: places are counted
+// the sort of most batches of up to kSmallTokens: places are counted
 // ---------------------------------------------------------------------------
 //
 // The place of position p in a sorted tile of the batch is the number of the
@@ -263,12 +295,11 @@ __global__ __launch_bounds__(kCoalThreads) void coal_scatter(SortPass a) {
 // every place is counted on its own, with no exchange between blocks.  One
 // launch sorts each tile so (all of the batch when it is one tile); another
 // then adds, for every position, the counts of the other tiles from binary
-// searches in them.  16384 tokens of a 128256-row table: 5.7 + 5.2 us, against
-// 25.8 us in the four launches of the radix sort; 65536 tokens: 12.7 + 23.6
-// against 36 us in four (the compares grow with the square of the batch, so
-// larger ones keep the radix sort).  One tile of up to 4096: 4.1 us at 1000
-// tokens.  Tiles of 2048 balance the two launches: half as large doubles the
-// searches, twice as large the compares.
+// searches in them.  16384 tokens of a 128256-row table: 5.4 + 5.4 us, against
+// 26 us in the four launches of the radix sort; 65536 tokens: 11.6 + 23.2
+// against 36 us in four (the searches grow with the square of the batch).  One
+// tile of up to 4096: 4.1 us at 1000 tokens.  Tiles of 2048 balance the two
+// launches: half as large doubles the searches, twice as large the compares.
 
 // Ids are compared as uint32 clamped into [0, V); kNoKey is above all of them.
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
@@ -513,10 +544,11 @@ __global__ __launch_bounds__(kCoalThreads) void coal_heads_write(HeadParams a) {
     }
 }
 
-// The same in one launch, for the batches of coal_rank: a block of 1024
+// The same in one launch, for batches of up to kSmallTokens: a block of 1024
 // threads per 1024 sorted entries, one each, that counts the heads of all
 // earlier entries itself (16 per thread and round) instead of waiting for
-// another launch to do it: 4.3 us at 16384 tokens against 2.7 + 4.4 us.
+// another launch to do it: 4.2 us at 16384 tokens against 4.0 + 4.4 us, 8.4 at
+// 65536 against 4.7 + 4.1 (and one launch less).
 constexpr int kHeadThreads = 1024;
 constexpr int kHeadWaves = kHeadThreads / kWave;
 
@@ -979,6 +1011,37 @@ CoalPlan coal_plan(int64_t P, int64_t V, int64_t D) {
     return c;
 }
 
+// Whether a batch's places are counted (coal_rank, coal_merge) or radix-sorted.
+// The counted sort costs 8.8 / 14.4 / 25.5 / 31.8 us with one to four rounds of
+// tiles in the merge's LDS, whatever the ids; a radix pass about 9-10.5 us with
+// digits of up to 8 bits, 10-15 with 9, 14.5-23 with 10, and 1-4 us more where its
+// offset loop (unrolled by 16 tiles) has a remainder.  Radix minus counted sort,
+// us, at 16384 / 24576 / 32768 / 40960 / 49152 / 57344 / 65536 tokens of one batch
+// (uniform ids, D = 64), by the table's id bits:
+//    1     -1.7   -4.6   -5.8  -14.4  -16.3  -21.2  -22.8
+//    8     -0.0   -2.7   -4.8  -12.3  -15.1  -19.1  -21.4
+//    9      2.0    0.6   -2.0   -8.0  -11.6  -13.0  -17.0
+//   10      5.7    6.4    3.0   -0.7   -5.2   -5.8   -9.0
+//   11      6.2    3.9    2.4   -4.3   -7.4  -10.7  -14.2
+//   16      8.8    6.4    4.8   -1.6   -4.7   -7.1  -11.0
+//   17     11.9   12.8   10.0    6.5    1.9    3.4   -2.6
+//   19     18.2   25.2   20.1   21.3   14.7   19.8   13.4
+//   21     13.8   14.5   12.5    5.5    2.1    1.3   -2.0
+//   24     18.2   15.8   14.5    8.3    5.6    4.5    1.0
+//   31     26.2   25.4   23.7   17.8   14.3   15.6   11.9
+// (smaller batches: counted or level in every row, by up to 44 us).  The weights below
+// reproduce the signs to within 2 us.
+bool coal_counted(int64_t P, int64_t V) {
+    if (P > kSmallTokens) return false;
+    const CoalPlan c = coal_plan(P, V, 1);
+    int pass = c.digit_bits <= 8 ? 4 : c.digit_bits == 9 ? 5 : 8;
+    if (c.digit_bits > 8 && c.ntiles % 16 != 0) ++pass;
+    constexpr int kLeast[] = {4, 6, 10, 12};   // by rounds of the merge
+    const int64_t per_round = (int64_t)kMergeTiles * kRankTile;
+    static_assert(kSmallTokens <= 4 * kMergeTiles * kRankTile, "a limit for every round");
+    return c.passes * pass >= kLeast[P > 0 ? (P - 1) / per_round : 0];
+}
+
 hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s) {
     const CoalPlan c = coal_plan(a.P, a.V, a.D);
     char* ws = a.ws;
@@ -998,10 +1061,10 @@ hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s) {
     // 1. sort
     const uint32_t* kin = nullptr;
     const uint32_t* vin = nullptr;
-    // Counted places (see coal_rank) where that is cheaper than the radix sort.
-    const bool small = a.P <= kRankMaxTokens;
+    const bool small = a.P <= kSmallTokens;
+    const bool counted = coal_counted(a.P, a.V);
     const int nrank = (int)((a.P + kWave - 1) / kWave);
-    if (small) {
+    if (counted) {
         const bool one = a.P <= kRankOneTile;
         RankParams p;
         p.tok = a.tok;
@@ -1031,7 +1094,7 @@ hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s) {
             vin = vb;
         }
     }
-    for (int q = 0; !small && q < c.passes; ++q) {
+    for (int q = 0; !counted && q < c.passes; ++q) {
         SortPass p;
         p.tok = q == 0 ? a.tok : nullptr;
         p.keys_in = kin;
@@ -1044,14 +1107,16 @@ hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s) {
         p.bits = c.digit_bits;
         p.ntiles = c.ntiles;
         p.hist = hist;
-        p.offs = offs;
+        p.offs = small ? nullptr : offs;
         p.tile_bad = tile_bad;
         coal_hist<<<c.ntiles, kCoalThreads, 0, s>>>(p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        coal_scan<<<1, 1024, 0, s>>>(hist, offs, (int64_t)c.ntiles << p.bits);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        if (!small) {
+            coal_scan<<<1, 1024, 0, s>>>(hist, offs, (int64_t)c.ntiles << p.bits);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
         coal_scatter<<<c.ntiles, kCoalThreads, 0, s>>>(p);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1071,11 +1136,12 @@ hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s) {
     h.idx = a.idx;
     h.n_out = a.n_out;
     h.fix_count = reinterpret_cast<uint32_t*>(ws + c.fix_count);
-    h.tile_bad = small ? hist : tile_bad;
+    h.tile_bad = counted ? hist : tile_bad;
     h.status = status;
     hipError_t e = hipSuccess;
     if (small) {
-        coal_heads_small<<<(unsigned)((a.P + kHeadThreads - 1) / kHeadThreads), kHeadThreads, 0, s>>>(h, nrank);
+        coal_heads_small<<<(unsigned)((a.P + kHeadThreads - 1) / kHeadThreads), kHeadThreads, 0, s>>>(
+            h, counted ? nrank : c.ntiles);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     } else {

@@ -265,6 +265,7 @@ struct CoalPlan {
     size_t total;      // workspace bytes
 };
 CoalPlan coal_plan(int64_t P, int64_t V, int64_t D);
+bool coal_counted(int64_t P, int64_t V);   // the batch's sort: counted places, or radix passes
 hipError_t launch_coalesce(const CoalArgs& a, hipStream_t s);
 
 } // namespace ember

@@ -1,5 +1,7 @@
 """Coalescing across the batch sizes where its sort, heads and sums change form
 (GPU), against exact sums: whole-number signals whose sums every order gives."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -150,3 +152,85 @@ def test_rows_of_an_id_are_added_in_position_order(P, D, V):
     assert three.sum() == ids
     assert np.array_equal(G[three, :3], np.tile(np.float32([0, 0, 1]), (ids, 1)))
     assert np.array_equal(G.view(np.uint32), G_o.view(np.uint32))
+
+
+# ---------------------------------------------------------------------------
+# which sort a batch of up to 64 sort tiles takes
+# ---------------------------------------------------------------------------
+
+SORT_TOKENS = (16384, 24576, 32768, 40960, 49152, 57344, 65536)
+# radix minus counted sort, us, measured on an MI355X, by the table's id bits
+RADIX_MINUS_COUNTED = {
+    1: (-1.7, -4.6, -5.8, -14.4, -16.3, -21.2, -22.8),
+    8: (0.0, -2.7, -4.8, -12.3, -15.1, -19.1, -21.4),
+    9: (2.0, 0.6, -2.0, -8.0, -11.6, -13.0, -17.0),
+    10: (5.7, 6.4, 3.0, -0.7, -5.2, -5.8, -9.0),
+    11: (6.2, 3.9, 2.4, -4.3, -7.4, -10.7, -14.2),
+    16: (8.8, 6.4, 4.8, -1.6, -4.7, -7.1, -11.0),
+    17: (11.9, 12.8, 10.0, 6.5, 1.9, 3.4, -2.6),
+    19: (18.2, 25.2, 20.1, 21.3, 14.7, 19.8, 13.4),
+    21: (13.8, 14.5, 12.5, 5.5, 2.1, 1.3, -2.0),
+    24: (18.2, 15.8, 14.5, 8.3, 5.6, 4.5, 1.0),
+    31: (26.2, 25.4, 23.7, 17.8, 14.3, 15.6, 11.9),
+}
+
+
+def counted(P, V):
+    fn = em.LIB._ZN5ember12coal_countedEll     # ember::coal_counted(int64_t, int64_t)
+    fn.argtypes, fn.restype = [ctypes.c_int64, ctypes.c_int64], ctypes.c_bool
+    return fn(P, V)
+
+
+def test_each_batch_takes_the_faster_sort():
+    for bits, row in RADIX_MINUS_COUNTED.items():
+        V = min(2 ** bits, 2 ** 31 - 2)
+        for P, d in zip(SORT_TOKENS, row):
+            assert counted(P, V) == (d > 0) or abs(d) <= 2.0, (bits, P, d)
+        for P in (1, 1000, 4096, 4097, 12288):
+            assert counted(P, V)
+        assert not counted(65537, V)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P", [16385, 20000, 32768, 32769, 49152, 49153, 61441, 65536])
+@pytest.mark.parametrize("V", [1, 2, 200, 257, 1000, 1500, 50021, 128256, 2 ** 20, 2 ** 21, 2 ** 21 + 1, 2 ** 31 - 2])
+def test_both_sorts_of_up_to_64_tiles(P, V):
+    D = 4
+    rng = np.random.default_rng(P + V)
+    tok = rng.integers(0, V, P).astype(np.int64)
+    tok[rng.random(P) < 0.2] = V - 1                 # one frequent id
+    U = torch.from_numpy(rng.integers(-8, 9, (P, D)).astype(np.float32)).to(DEV)
+    co = em.Coalescer(P, V, D, dtype=torch.float32, device=DEV)
+    print(f"coalesce P={P} V={V} counted={counted(P, V)}", flush=True)
+    for bad_at in (P - 1, P // 2, 0):                # reported, and the workspace works on
+        bad = tok.copy()
+        bad[bad_at] = V if bad_at else -1
+        em.ember_coalesce_rows(torch.from_numpy(bad).to(DEV), U, V, co.idx, co.G_rows, co.n_out, co.ws)
+        assert em.ember_get_error(co.ws) == em.EMBER_ERR_INDEX and int(co.n_out.item()) == -1
+    idx, G = co(torch.from_numpy(tok).to(DEV), U)
+    want, inv = np.unique(tok, return_inverse=True)
+    assert np.array_equal(idx.cpu().numpy(), want)
+    sums = np.zeros((want.size, D))
+    np.add.at(sums, inv, U.cpu().numpy().astype(np.float64))
+    assert np.array_equal(G.cpu().numpy().astype(np.float64), sums)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P", [65537, 70001])
+@pytest.mark.parametrize("V", [1000, 2 ** 20, 2 ** 21 + 5, 2 ** 30, 2 ** 31 - 2])    # 1, 2, 3, 3 and 4 radix passes
+def test_radix_passes_past_64_tiles(P, V):
+    tok, U = np.random.default_rng(V).integers(0, V, P), np.random.default_rng(P).standard_normal((P, 4))
+    tok[::7] = tok[3]
+    U = torch.from_numpy(U.astype(np.float32)).to(DEV)
+    co = em.Coalescer(P, V, 4, dtype=torch.float32, device=DEV)
+    print(f"coalesce P={P} V={V}", flush=True)
+    idx, G = co(torch.from_numpy(tok).to(DEV), U)
+    want, inv = np.unique(tok, return_inverse=True)
+    assert np.array_equal(idx.cpu().numpy(), want)
+    U64 = U.cpu().numpy().astype(np.float64)
+    sums, mags = np.zeros((want.size, 4)), np.zeros((want.size, 4))
+    np.add.at(sums, inv, U64)
+    np.add.at(mags, inv, np.abs(U64))
+    # one rounding to fp32 of a float64 sum within (count - 1) 2^-53 sum|u| of the exact one, on both sides
+    bound = 2.0 ** -24 * np.abs(sums) + 2 * P * 2.0 ** -53 * mags + 2.0 ** -149
+    assert (np.abs(G.cpu().numpy().astype(np.float64) - sums) <= bound).all()
