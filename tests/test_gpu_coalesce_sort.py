@@ -234,3 +234,51 @@ def test_radix_passes_past_64_tiles(P, V):
     # one rounding to fp32 of a float64 sum within (count - 1) 2^-53 sum|u| of the exact one, on both sides
     bound = 2.0 ** -24 * np.abs(sums) + 2 * P * 2.0 ** -53 * mags + 2.0 ** -149
     assert (np.abs(G.cpu().numpy().astype(np.float64) - sums) <= bound).all()
+
+
+# ---------------------------------------------------------------------------
+# special values through every form of the sums
+# ---------------------------------------------------------------------------
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V", [40, 100003])     # fewer rows than positions, and more
+@pytest.mark.parametrize("D", [1, 2, 3, 4, 5, 7, 255, 256, 257, 1021])
+@pytest.mark.parametrize("ud,gd", [(torch.float32, torch.float32), (torch.bfloat16, torch.bfloat16),
+                                   (torch.bfloat16, torch.float32), (torch.float32, torch.bfloat16)])
+def test_special_values_in_every_form_of_the_sums(ud, gd, D, V):
+    import oracle
+    from parity_checks import bf16_values, host_bits
+    from test_oracle_coalesce_pins import BF16_EDGE_SEGMENTS
+    # fp32 bits of each id's rows; +-inf, NaN and -0 also in segments that chunks cut
+    segs = [[b << 16 for b in rows] for rows, _ in BF16_EDGE_SEGMENTS]
+    segs += [[0x7FC10000], [0x80000000] * 150, [0x3F800000] * 99 + [0x7F800000] + [0x3F800000] * 60,
+             [0x7F800000] + [0x3F800000] * 120 + [0xFF800000], [0x00010000] * 130]
+    if ud == torch.float32:
+        segs += [[0x3F808008], [0x3F808000], [0x3F818000], [0x00000001], [0x00008001], [0x80000000],
+                 [0x7F7FFFFF, 0x7F7FFFFF], [0x00000001] * 140]
+    ids = np.sort(np.random.default_rng(D).choice(V, len(segs), replace=False)).astype(np.int64)
+    tok = np.concatenate([np.full(len(r), k, np.int64) for k, r in zip(ids, segs)])
+    rows = np.concatenate([np.array(r, np.uint64) for r in segs]).astype(np.uint32)
+    perm = np.random.default_rng(9).permutation(tok.size)
+    tok, rows = tok[perm], rows[perm]
+    cols = np.stack([rows ^ (0x80000000 if j % 2 else 0) for j in range(D)], axis=1).astype(np.uint32)
+    host = (cols >> 16).astype(np.uint16) if ud == torch.bfloat16 else cols.view(np.float32)
+    q = 16 // torch.empty(0, dtype=ud).element_size()
+    U = torch.full((tok.size, (D + q - 1) // q * q), float("nan"), dtype=ud, device=DEV)[:, :D]
+    src = torch.from_numpy(host.view(np.int16) if ud == torch.bfloat16 else host).to(DEV)
+    U.copy_(src.view(torch.bfloat16) if ud == torch.bfloat16 else src)
+    co = em.Coalescer(tok.size, V, D, dtype=gd, device=DEV)
+    pad = co.G_rows._base if co.G_rows._base is not None else co.G_rows
+    pad.fill_(7.0)
+    print(f"coalesce specials D={D} V={V} {ud}->{gd}", flush=True)
+    idx, G = co(torch.from_numpy(tok).to(DEV), U)
+    st, idx_o, want = oracle.coalesce(tok, host, V, out_dtype=np.uint16 if gd == torch.bfloat16 else np.float32)
+    assert st == oracle.OK and np.array_equal(idx.cpu().numpy(), idx_o)
+    got = host_bits(G)
+    gv, wv = (bf16_values(got), bf16_values(want)) if gd == torch.bfloat16 else (got, want)
+    nan = np.isnan(wv)
+    assert np.array_equal(np.isnan(gv), nan)
+    gb, wb = (got, want) if gd == torch.bfloat16 else (got.view(np.uint32), want.view(np.uint32))
+    bad = np.argwhere((gb != wb) & ~nan)      # every sum is exact in float64: the same bits
+    assert bad.size == 0, bad[:4].tolist()
+    assert bool((pad[:, D:] == 7.0).all()) and bool((pad[ids.size:] == 7.0).all())
