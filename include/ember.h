@@ -350,8 +350,7 @@ int ember_rowonly_step_sparse_rows_devn(void* W, int w_dtype, int64_t ldw,
  * device-count step refuses, leaving its table untouched); idx and G_rows are
  * then unspecified.  n_tok = 0 gives n = 0 (tok, U, idx, G_rows may
  * then be NULL).  Layout and alignment rules of U and G_rows are those of W
- * and G (the padding of a row of U inside the 16-byte chunk that holds its last
- * element may be read, but never affects a result); tok, idx and n_out must be 8-byte aligned.
+ * and G; tok, idx and n_out must be 8-byte aligned.
  *
  * The workspace (device, 256-byte aligned, ember_coalesce_workspace_bytes of
  * at least n_tok tokens) needs no initialisation and may be reused by

@@ -655,6 +655,17 @@ template <typename T> struct Cols {
             }
         }
     }
+    // the columns that the first lanes hold one each, as every lane's row
+    static __device__ __forceinline__ raw collect(uint32_t w) {
+        raw r = {};
+#pragma unroll
+        for (int e = 0; e < kColsPerLane - 1; ++e) {
+            const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)w, e);
+            if constexpr (sizeof(T) == 4) r[e] = x;
+            else r[e / 2] |= x << (16 * (e & 1));
+        }
+        return r;
+    }
 };
 
 // float64 -> bf16, one round-to-nearest-even.  Rounding to fp32 (nearest-even)
@@ -690,9 +701,12 @@ __device__ __forceinline__ uint32_t f32_bits_to_bf16(uint32_t w) {
 }
 
 // Stores of one lane's 4 columns through a buffer resource whose length is the
-// row's whole groups of 4 columns: the hardware drops the stores of lanes past
-// it, so no lane-divergent branch is needed.  Where D is not a multiple of 4
-// (kExact false) the lane that holds the rest stores it element by element.
+// row's D columns: the hardware drops the stores of lanes past it, so no
+// lane-divergent branch is needed.  Where D is not a multiple of 4 the lane of
+// the last columns holds columns D - 4 .. D - 1, some of them the same values
+// as its neighbour's; a row of fewer than 4 columns (kNarrow) is stored element
+// by element.
+enum Width { kExact, kRagged, kNarrow };   // D a multiple of 4, not one, below 4
 constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit data format, gfx9 family
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(void* row, int64_t bytes) {
@@ -700,37 +714,38 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(void* row, int64_t by
 }
 
 // One lane's columns of row u of G, already in G's format (kWords words).
-template <typename GT, bool kExact>
+template <typename GT, Width kW>
 __device__ __forceinline__ void buf_store_words(void* G, int64_t ldg, uint32_t u, int col, int64_t D,
                                                 const uint32_t (&w)[Cols<GT>::kWords]) {
     GT* row = static_cast<GT*>(G) + (int64_t)u * ldg;
-    const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, (kExact ? D : D / kColsPerLane * kColsPerLane) * (int64_t)sizeof(GT));
-    using v4 = decltype(__builtin_amdgcn_raw_buffer_load_b128(rs, 0, 0, 0));
-    using v2 = decltype(__builtin_amdgcn_raw_buffer_load_b64(rs, 0, 0, 0));
-    constexpr int kW = Cols<GT>::kWords;
-    const int byte0 = col * (int)sizeof(GT);
-    if constexpr (kW % 4 == 0) {
-#pragma unroll
-        for (int g = 0; g < kW; g += 4)
-            __builtin_amdgcn_raw_buffer_store_b128(v4{w[g], w[g + 1], w[g + 2], w[g + 3]}, rs, byte0 + 4 * g, 0, 0);
-    } else {
-        static_assert(kW == 2, "4 bf16 columns per lane");
-        __builtin_amdgcn_raw_buffer_store_b64(v2{w[0], w[1]}, rs, byte0, 0, 0);
-    }
-    if constexpr (!kExact) {
-        if (col < D && col + kColsPerLane > D) {
+    if constexpr (kW == kNarrow) {
+        if (col == 0) {
 #pragma unroll
             for (int e = 0; e < kColsPerLane - 1; ++e) {
-                if (col + e >= D) break;
-                if constexpr (sizeof(GT) == 4) row[col + e] = __uint_as_float(w[e]);
-                else row[col + e] = (GT)(w[e / 2] >> (16 * (e & 1)));
+                if (e >= D) break;
+                if constexpr (sizeof(GT) == 4) row[e] = __uint_as_float(w[e]);
+                else row[e] = (GT)(w[e / 2] >> (16 * (e & 1)));
             }
         }
+        return;
+    }
+    const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, D * (int64_t)sizeof(GT));
+    using v4 = decltype(__builtin_amdgcn_raw_buffer_load_b128(rs, 0, 0, 0));
+    using v2 = decltype(__builtin_amdgcn_raw_buffer_load_b64(rs, 0, 0, 0));
+    constexpr int kWords = Cols<GT>::kWords;
+    const int byte0 = col * (int)sizeof(GT);
+    if constexpr (kWords % 4 == 0) {
+#pragma unroll
+        for (int g = 0; g < kWords; g += 4)
+            __builtin_amdgcn_raw_buffer_store_b128(v4{w[g], w[g + 1], w[g + 2], w[g + 3]}, rs, byte0 + 4 * g, 0, 0);
+    } else {
+        static_assert(kWords == 2, "4 bf16 columns per lane");
+        __builtin_amdgcn_raw_buffer_store_b64(v2{w[0], w[1]}, rs, byte0, 0, 0);
     }
 }
 
 // A finished float64 sum, rounded once to G's type.
-template <typename GT, bool kExact>
+template <typename GT, Width kW>
 __device__ __forceinline__ void buf_store_cols(void* G, int64_t ldg, uint32_t u, int col, int64_t D,
                                                const double (&x)[kColsPerLane]) {
     uint32_t w[Cols<GT>::kWords];
@@ -739,14 +754,14 @@ __device__ __forceinline__ void buf_store_cols(void* G, int64_t ldg, uint32_t u,
         if constexpr (sizeof(GT) == 4) w[e] = __float_as_uint((float)x[e]);
         else w[e] = (uint32_t)f64_to_bf16(x[2 * e]) | ((uint32_t)f64_to_bf16(x[2 * e + 1]) << 16);
     }
-    buf_store_words<GT, kExact>(G, ldg, u, col, D, w);
+    buf_store_words<GT, kW>(G, ldg, u, col, D, w);
 }
 
 // A segment of one row: its sum is that row's value, which G's type holds
 // exactly when the types agree (else one rounding, fp32 -> bf16), so the
 // value is converted without float64 arithmetic; -0 and NaN come out as the
 // float64 sum gives them.
-template <typename UT, typename GT, bool kExact>
+template <typename UT, typename GT, Width kW>
 __device__ __forceinline__ void buf_store_one_row(void* G, int64_t ldg, uint32_t u, int col, int64_t D,
                                                   const typename Cols<UT>::raw& r) {
     uint32_t f[kColsPerLane];   // fp32 bits per column
@@ -761,7 +776,7 @@ __device__ __forceinline__ void buf_store_one_row(void* G, int64_t ldg, uint32_t
         if constexpr (sizeof(GT) == 4) w[e] = f[e];
         else w[e] = f32_bits_to_bf16(f[2 * e]) | (f32_bits_to_bf16(f[2 * e + 1]) << 16);
     }
-    buf_store_words<GT, kExact>(G, ldg, u, col, D, w);
+    buf_store_words<GT, kW>(G, ldg, u, col, D, w);
 }
 
 __device__ __forceinline__ void store_partial(double* row, int64_t col, int64_t D, const double (&x)[kColsPerLane]) {
@@ -792,16 +807,17 @@ __device__ __forceinline__ int64_t chunk_start(const SumParams& a, int64_t c, ui
 // and start first, while the long segments of the frequent ids, which only
 // stream rows, fill the slots that free up.
 // The wavefront loads kRunRows rows at a time into registers (lanes past D read
-// column 0 and store nothing; where D is not a multiple of 4 the lane that
-// holds a row's last columns reads its whole group, which lies inside one
-// 16-byte chunk of the row, and stores only the columns below D), then walks
-// them in order; a row that starts a segment resets the sum, a row that ends
-// one stores it.  Segment boundaries depend only on the sorted ids, so every
+// column 0 and store nothing; where D is not a multiple of 4 the lane of the
+// last columns takes columns D - 4 .. D - 1, so that nothing past column D is
+// read, and repeats some of its neighbour's sums; of rows of fewer than 4
+// columns each lane loads one and lane 0 collects them), then walks them in
+// order; a row that starts a segment resets the sum, a row that ends one
+// stores it.  Segment boundaries depend only on the sorted ids, so every
 // branch is uniform across the wavefront.
 // kSingles (batches of mostly one-row segments): a segment of one row is found
 // before its row is widened and added; otherwise it is found at its end, which
 // spares the rows of longer segments the extra branches.
-template <typename UT, typename GT, bool kExact, bool kSingles>
+template <typename UT, typename GT, Width kW, bool kSingles>
 __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
     using raw = typename Cols<UT>::raw;
     const int lane = threadIdx.x & (kWave - 1);
@@ -810,8 +826,9 @@ __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
     if (ci >= a.nchunks) return;
     const int slab = item - ci * a.nslabs;
     const int c = a.nchunks - 1 - ci;
-    const int64_t col = (int64_t)slab * kSlabCols + (int64_t)lane * kColsPerLane;
-    const bool col_ok = col < a.D;
+    const int64_t col0 = (int64_t)slab * kSlabCols + (int64_t)lane * kColsPerLane;
+    const bool col_ok = col0 < a.D;
+    const int64_t col = kW == kRagged && col_ok ? min(col0, a.D - kColsPerLane) : col0;
     uint32_t seg0, seg1;
     int64_t start0, start1;
     const int64_t k0 = chunk_start(a, c, seg0, start0);
@@ -825,7 +842,7 @@ __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
     // the chunk's first segment began earlier and ends here: list the chunk
     // for the launch that adds the pieces (once, from the first slab)
     bool ends_crossing = false;
-    const int64_t colc = col_ok ? col : 0;
+    const int64_t colc = kW == kNarrow ? (lane < a.D ? lane : 0) : (col_ok ? col : 0);
     // ids, positions and segment numbers of a batch, one per lane (lane nr
     // holds the id after the batch, if any); read back per row with lane
     // reads instead of a memory round trip per row.  The next batch's are
@@ -847,10 +864,25 @@ __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
 #pragma unroll
         for (int r = 0; r < kRunRows; ++r) {
             const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)pv, r < nr ? r : 0);
-            rows[r] = *reinterpret_cast<const raw*>(U + (int64_t)p * a.ldu + colc);
+            const UT* const at = U + (int64_t)p * a.ldu + colc;
+            if constexpr (kW == kExact) {
+                rows[r] = *reinterpret_cast<const raw*>(at);
+            } else if constexpr (kW == kNarrow) {
+                UT one;
+                __builtin_memcpy(&one, at, sizeof(UT));
+                uint32_t w = 0;
+                __builtin_memcpy(&w, &one, sizeof(UT));
+                rows[r][0] = w;
+            } else {
+                __builtin_memcpy(&rows[r], at, sizeof(raw));   // aligned to an element only
+            }
         }
         uint32_t kn, pn, un;
         batch_meta(s0 + kRunRows, kn, pn, un);
+        if constexpr (kW == kNarrow) {
+#pragma unroll
+            for (int r = 0; r < kRunRows; ++r) rows[r] = Cols<UT>::collect(rows[r][0]);
+        }
 #pragma unroll
         for (int r = 0; r < kRunRows; ++r) {
             const int64_t k = s0 + r;
@@ -869,7 +901,7 @@ __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
                 if (kSingles && ends && run0 == k && !piece) {
                     // a segment of this row alone: no float64 arithmetic
                     const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)uv, r);
-                    buf_store_one_row<UT, GT, kExact>(a.G, a.ldg, u, (int)col, a.D, rows[r]);
+                    buf_store_one_row<UT, GT, kW>(a.G, a.ldg, u, (int)col, a.D, rows[r]);
                     continue;
                 }
                 double x[kColsPerLane];
@@ -882,10 +914,10 @@ __global__ __launch_bounds__(kCoalThreads) void coal_segsum(SumParams a) {
                         ends_crossing |= first && !(chunk_end && ends_after);
                     } else if (!kSingles && run0 == k) {
                         const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)uv, r);
-                        buf_store_one_row<UT, GT, kExact>(a.G, a.ldg, u, (int)col, a.D, rows[r]);
+                        buf_store_one_row<UT, GT, kW>(a.G, a.ldg, u, (int)col, a.D, rows[r]);
                     } else {
                         const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)uv, r);
-                        buf_store_cols<GT, kExact>(a.G, a.ldg, u, (int)col, a.D, acc);
+                        buf_store_cols<GT, kW>(a.G, a.ldg, u, (int)col, a.D, acc);
                     }
                 }
             }
@@ -965,11 +997,14 @@ template <typename UT, typename GT>
 void launch_segsum(const SumParams& m, int64_t V, unsigned grid, hipStream_t s) {
     const bool singles = m.P <= V;
     if (m.D % kColsPerLane == 0) {
-        if (singles) coal_segsum<UT, GT, true, true><<<grid, kCoalThreads, 0, s>>>(m);
-        else coal_segsum<UT, GT, true, false><<<grid, kCoalThreads, 0, s>>>(m);
+        if (singles) coal_segsum<UT, GT, kExact, true><<<grid, kCoalThreads, 0, s>>>(m);
+        else coal_segsum<UT, GT, kExact, false><<<grid, kCoalThreads, 0, s>>>(m);
+    } else if (m.D > kColsPerLane) {
+        if (singles) coal_segsum<UT, GT, kRagged, true><<<grid, kCoalThreads, 0, s>>>(m);
+        else coal_segsum<UT, GT, kRagged, false><<<grid, kCoalThreads, 0, s>>>(m);
     } else {
-        if (singles) coal_segsum<UT, GT, false, true><<<grid, kCoalThreads, 0, s>>>(m);
-        else coal_segsum<UT, GT, false, false><<<grid, kCoalThreads, 0, s>>>(m);
+        if (singles) coal_segsum<UT, GT, kNarrow, true><<<grid, kCoalThreads, 0, s>>>(m);
+        else coal_segsum<UT, GT, kNarrow, false><<<grid, kCoalThreads, 0, s>>>(m);
     }
 }
 

@@ -282,3 +282,28 @@ def test_special_values_in_every_form_of_the_sums(ud, gd, D, V):
     bad = np.argwhere((gb != wb) & ~nan)      # every sum is exact in float64: the same bits
     assert bad.size == 0, bad[:4].tolist()
     assert bool((pad[:, D:] == 7.0).all()) and bool((pad[ids.size:] == 7.0).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [1, 2, 3, 5, 6, 7, 253, 254, 255, 257, 258, 259, 1027])
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_last_row_may_end_with_the_storage(dt, D):
+    # only the D columns of a row belong to it: U's storage ends with its last
+    # element, and what the padding of the other rows holds does not matter
+    P, V = 333, 100
+    rng = np.random.default_rng(D)
+    q = 16 // torch.empty(0, dtype=dt).element_size()
+    ld = (D + q - 1) // q * q + q
+    flat = torch.full(((P - 1) * ld + D,), float("nan"), dtype=dt, device=DEV)
+    U = flat.as_strided((P, D), (ld, 1))
+    U.copy_(torch.from_numpy(rng.integers(-4, 5, (P, D)).astype(np.float32)).to(DEV))
+    tok = rng.integers(0, V, P).astype(np.int64)
+    tok[-1] = V                                          # a segment of the last row alone
+    co = em.Coalescer(P, V + 1, D, dtype=dt, device=DEV)
+    print(f"coalesce tight D={D} {dt}", flush=True)
+    idx, G = co(torch.from_numpy(tok).to(DEV), U)
+    want, inv = np.unique(tok, return_inverse=True)
+    sums = np.zeros((want.size, D))
+    np.add.at(sums, inv, U.float().cpu().numpy().astype(np.float64))
+    assert np.array_equal(idx.cpu().numpy(), want)
+    assert np.array_equal(G.float().cpu().numpy().astype(np.float64), sums)   # |sum| <= 256: exact in bf16
