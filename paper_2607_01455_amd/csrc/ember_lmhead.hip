@@ -74,6 +74,15 @@ constexpr int kStages = 4;                      // LDS stages (steps in flight)
 // 3610 / 3570 / 3605).
 constexpr int kGroupMShort = 8, kGroupMLong = 2;
 constexpr int64_t kGroupShortT = 4096;          // longest contraction of the wide groups
+// Small tables with a ragged last row tile take the narrow groups at any T: the
+// blocks of that tile take the checked epilogue, some 2 us longer, and one wide
+// group would give one to nearly every XCD (whole step, fp32, us, groups of
+// 8 / 2 at T = 64 and 256: 1000 x 2048 34.3 / 32.3 and 36.9 / 34.5 (33.5 and 36.0
+// when every block checked), 1500 x 1792 37.0 / 34.3 and 39.4 / 36.7, 2000 x 3072
+// 44.0 / 41.8 and, at T = 512, 50.6 / 49.1).  With whole row tiles there is no such difference
+// (1024 x 2048 within 0.6 us either way), and past 12 column tiles the wide
+// groups win again (1000 x 4096 38.4 / 40.8).
+constexpr int kRaggedMT = 8, kRaggedNT = 12;
 // An fp32 G that does not fit the 256 MB last-level cache is stored
 // non-temporally: the apply pass would not find most of it there, and the
 // operands keep their place (whole step, us, cached / non-temporal: 32000 x 4096
@@ -528,7 +537,8 @@ hipError_t launch_lmhead_grad(const LmheadArgs& x, hipStream_t s) {
     p.P = x.P;
     p.MT = pl.MT;
     p.NT = pl.NT;
-    p.group_m = x.T <= kGroupShortT ? kGroupMShort : kGroupMLong;
+    const bool few_ragged = x.V % kBM != 0 && pl.MT <= kRaggedMT && pl.NT <= kRaggedNT;
+    p.group_m = x.T <= kGroupShortT && !few_ragged ? kGroupMShort : kGroupMLong;
     p.stream_g = x.g_dtype == 0 && x.V * x.D * 4 > kStreamGBytes;
     const int64_t total = (int64_t)pl.MT * pl.NT;
     const int64_t per_launch = kMaxGridBlocks;   // a multiple of kXcds

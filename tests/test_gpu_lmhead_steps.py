@@ -17,6 +17,10 @@ pytestmark = pytest.mark.gpu
     (4096, 2305, 520, torch.float32),   # last of the wide groups, 10 x 3 tiles: groups of 8 and 2
     (4097, 2305, 520, torch.bfloat16),  # first of the narrow groups
     (33, 16389, 4096, torch.float32),   # past 256 MB of fp32 G: streamed, the last row tile ragged
+    (96, 2001, 3072, torch.float32),    # 8 x 12 tiles, the last row tile ragged: narrow groups
+    (96, 2001, 3080, torch.float32),    # 13 column tiles, and
+    (96, 2048, 520, torch.bfloat16),    # whole row tiles, and
+    (96, 2051, 520, torch.bfloat16),    # 9 row tiles: wide groups
 ])
 def test_token_steps_are_exact(T, V, D, gd):
     from paper_2607_01455_amd import ember
