@@ -80,9 +80,9 @@ typedef enum {
 #define EMBER_MAX_V ((int64_t)0x7FFFFFFE)
 #define EMBER_MAX_D ((int64_t)(1 << 22))
 #define EMBER_MAX_TOKENS ((int64_t)(1 << 26))
-/* ember_lmhead_step: row strides of dY and H below 2^24 elements (a 64-token
- * slice of either is then addressable with 32-bit offsets), and at most 2^30
- * tokens. */
+/* ember_lmhead_step: row strides of dY and H below 2^24 elements (the slice of
+ * one token step of either is then addressable with 32-bit offsets), and at
+ * most 2^30 tokens. */
 #define EMBER_LMHEAD_MAX_LD ((int64_t)(1 << 24))
 #define EMBER_LMHEAD_MAX_T ((int64_t)(1 << 30))
 

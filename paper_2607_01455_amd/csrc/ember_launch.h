@@ -40,7 +40,7 @@ int64_t capped_blocks(int64_t blocks);
 // LM-head gradient GEMM tiles (ember_lmhead.hip): kLmheadTile x kLmheadTile
 // tiles of G, kLmheadK tokens per step.
 constexpr int kLmheadTile = 256;
-constexpr int kLmheadK = 64;        // tokens per step
+constexpr int kLmheadK = 32;        // tokens per step
 
 // Status bits written by the sparse statistics pass.
 constexpr int kFlagRange = 1;

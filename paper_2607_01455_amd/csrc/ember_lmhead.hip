@@ -63,7 +63,7 @@ constexpr int kWavesN = 2;                      // wave grid over the tile: kWav
 constexpr int kWavesM = kGemmWaves / kWavesN;
 constexpr int kBM = kLmheadTile;        // rows of G per block (vocabulary)
 constexpr int kBN = kLmheadTile;        // columns of G per block (hidden)
-constexpr int kBK = kLmheadK / 2;       // tokens per step: half of the slice that 32-bit offsets allow for
+constexpr int kBK = kLmheadK;           // tokens per step
 constexpr int kStages = 4;                      // LDS stages (steps in flight)
 // Row tiles per group of the tile order: the 32 tiles an XCD runs at a time
 // are 2 x 16 (long contractions) or 8 x 4 of row by column tiles.  8 x 4 reads
@@ -105,6 +105,7 @@ constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit data format, gfx9 family
 
 static_assert(kBM == kBN, "both operand slices share one LDS layout");
 static_assert(kBM == 256 && kBK % 16 == 0, "wave tiling assumes 256 x 256 tiles");
+static_assert((kBK + 1) * EMBER_LMHEAD_MAX_LD * 2 < (int64_t)1 << 31, "32-bit load offsets");
 static_assert(kGemmWaves == 8, "8 wavefronts per block");
 static_assert(kStages >= 2 && kLoadsPerWave * kRowsPerLoad * kGemmWaves == kBK, "load split");
 static_assert(kStages * kStageBytes <= 160 * 1024, "LDS of one CU");
@@ -449,15 +450,21 @@ __global__ __launch_bounds__(kThreads) void ember_lmhead_grad(Params a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.0f;
 
-    // Step kt multiplies stage kt % 2 in four 16-token sub-steps.  While the
-    // MFMAs of a sub-step run, the operands of the next one are read into the
-    // other register set, one operand behind each MFMA (without the fences the
-    // scheduler fetches every operand just before its MFMA and waits for it).
-    // The block barrier sits before the last sub-step, whose operands are in
-    // registers by then: past it every wave has read all of stage kt % 2 and
-    // step kt + 1 lies in the other stage, so the last sub-step's MFMAs cover
-    // both the first operand reads of step kt + 1 and the loads of step
-    // kt + 2 into the freed stage, which have a whole step to arrive.
+    // Step kt multiplies stage kt % kStages in kSub 16-token sub-steps.  While
+    // the MFMAs of a sub-step run, the operands of the next one are read into
+    // the other register set, one operand behind each MFMA (without the fences
+    // the scheduler fetches every operand just before its MFMA and waits for it).
+    // The block barrier (wait_step) sits before the last sub-step, whose
+    // operands are in registers by then.  Each wave comes to it with
+    //  - all of its LDS reads returned, so past the barrier no wave reads stage
+    //    kt % kStages any more, and the loads of step kt + kStages may fill it;
+    //  - at most (kStages - 2) 2 kLoadsPerWave of its loads outstanding.  Steps
+    //    up to kt + kStages - 1 have been issued and loads complete in order,
+    //    so those are of steps kt + 2 and later: past the barrier every wave's
+    //    part of step kt + 1 lies in stage (kt + 1) % kStages.
+    // The last sub-step's MFMAs then cover the first operand reads of step
+    // kt + 1 and the issue of the loads of step kt + kStages, which have
+    // kStages - 1 steps to arrive.
     bf16x8 af[2][kMT], bfr[2][kNT];
     auto step = [&](int kt, auto sc) {
         constexpr int k = decltype(sc)::value;
