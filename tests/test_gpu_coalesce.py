@@ -51,9 +51,9 @@ def run_case(em, tok_h: np.ndarray, U: torch.Tensor, V: int, g_dtype, what: str)
     (1000, 50, 64, torch.bfloat16, torch.bfloat16, 2),    # segments across chunks
     (3000, 4, 128, torch.bfloat16, torch.float32, 3),     # few very long segments
     (5000, 20000, 300, torch.float32, torch.float32, 4),  # mostly single rows, ragged slab
-    (17000, 128256, 256, torch.bfloat16, torch.bfloat16, 5),  # several sort tiles, three passes
-    (70000, 1000, 8, torch.float32, torch.bfloat16, 6),   # more than 64 tiles: separate scans
-    (4096, 2 ** 31 - 2, 16, torch.bfloat16, torch.bfloat16, 7),  # 31-bit ids, four passes
+    (17000, 128256, 256, torch.bfloat16, torch.bfloat16, 5),  # counted sort, several tiles
+    (70000, 1000, 8, torch.float32, torch.bfloat16, 6),   # radix sort, more than 64 tiles: separate scans
+    (4096, 2 ** 31 - 2, 16, torch.bfloat16, torch.bfloat16, 7),  # 31-bit ids, counted sort of one tile
 ])
 def test_coalesce_small_every_element(em, P, V, D, ud, gd, seed):
     rng = np.random.default_rng(seed)
@@ -153,7 +153,7 @@ def test_coalesce_index_errors_empty_batch_and_reuse(em):
 
 @pytest.mark.parametrize("P", [65536, 65537, 70000])
 def test_coalesce_index_error_and_recovery_many_tiles(em, P):
-    # 64 sort tiles (offsets derived in the blocks) and more (separate scans):
+    # radix sort of 64 tiles (offsets derived in the blocks) and of more (separate scans):
     # an id outside [0, V) in the last tile is reported, n = -1, and the same
     # workspace then coalesces a valid batch
     D, V = 8, 5000

@@ -287,3 +287,13 @@ def test_captured_count_choice_replays_bitwise(em):
         assert em.ember_get_error(A.ws) == em.EMBER_OK and em.ember_get_error(B.ws) == em.EMBER_OK
         assert int(A.ws[28:32].view(torch.int32).item()) == (1 if n <= 5120 else 0)
         _tables_equal((W, A.r, A.c), (W2, B.r, B.c))
+
+
+def test_binding_takes_the_current_stream(em):
+    x = torch.zeros(1, device=DEV)
+    assert em._stream(x) == torch.cuda.current_stream(x.device).cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert em._stream(x) == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+    with pytest.raises((ValueError, RuntimeError)):
+        em._stream(torch.zeros(1))

@@ -1,7 +1,7 @@
-"""LM-head gradient GEMM at the edges of its token steps: token counts around
+"""LM-head gradient GEMM at the edges of its token steps (token counts around
 one step (32), a round of the stage ring (128) and the change of tile order
-(4096), with small integers as data, so that every fp32 sum is exact in any
-order and G is the exact sum rounded once, bit for bit."""
+(4096)), with small integers as data, so that every fp32 sum is exact in any
+order and G is the exact sum rounded once, bit for bit; and G's special values."""
 import pytest
 import torch
 
@@ -46,3 +46,37 @@ def test_token_steps_are_exact(T, V, D, gd):
     for got, ref in ((tab.r, sq.mean(1)), (tab.c, sq.mean(0))):
         ref = (1.0 - b2) * ref
         assert ((got.cpu().double() - ref).abs() <= 1e-5 * ref).all()
+
+
+@pytest.mark.parametrize("V,D", [(256, 256), (70, 40)])     # a whole tile, and the checked epilogue
+@pytest.mark.parametrize("gd", [torch.float32, torch.bfloat16])
+def test_special_values_of_g(gd, V, D):
+    # column j of H is one-hot-like, so G_ij adds at most three exact products:
+    # bf16 midpoints and their neighbours, overflow, infinities, NaN, subnormals
+    from paper_2607_01455_amd import ember
+    big = 2.0 ** 127
+    sums = [(1.0, 2.0 ** -8, 0.0), (1.0, 2.0 ** -8, 2.0 ** -20), (1.0, 2.0 ** -8, -2.0 ** -20), (1.0, 2.0 ** -7, 2.0 ** -8),
+            (-1.0, -2.0 ** -8, -2.0 ** -20), (big * (2 - 2.0 ** -7), 2.0 ** 119, 0.0), (big * (2 - 2.0 ** -7), 2.0 ** 118, 0.0),
+            (big, big, 0.0), (-big, -big, 0.0), (float("inf"), 1.0, 0.0), (float("inf"), float("-inf"), 0.0),
+            (float("nan"), 1.0, 0.0), (2.0 ** -126, 0.0, 0.0), (2.0 ** -133, 0.0, 0.0), (-2.0 ** -130, 2.0 ** -133, 0.0),
+            (0.0, 0.0, 0.0)]
+    T = 3
+    dY = torch.zeros(T, V)
+    dY[:, :len(sums)] = torch.tensor(sums).t()
+    H = torch.ones(T, D)
+    H[:, 1] = -1.0
+    G = torch.full((V, D), 5.0, dtype=gd, device=DEV)
+    W = torch.zeros(V, D, dtype=torch.bfloat16, device=DEV)
+    tab = ember.EmberTable(V, D, device=DEV, lr=LR, beta2=B2, eps=EPS)
+    print(f"lmhead specials {gd} {V}x{D}", flush=True)
+    dYd = torch.zeros(T, (V + 7) // 8 * 8, dtype=torch.bfloat16, device=DEV)[:, :V]
+    dYd.copy_(dY.to(DEV))
+    tab.step_lmhead(W, dYd, H.bfloat16().to(DEV), G)
+    want32 = torch.zeros(V, D)
+    for t in range(T):
+        want32 += dY[t].bfloat16().float()[:, None] * H[t][None, :]
+    want = want32.to(gd)
+    got = G.cpu()
+    nan = torch.isnan(want)
+    assert torch.equal(torch.isnan(got), nan)
+    assert torch.equal(got[~nan], want[~nan])
