@@ -27,14 +27,13 @@
 // step barrier too, so no MFMA waits for an LDS read it follows directly.
 //
 // What bounds it: operand delivery and power.  At 128256 x 4096 x 16384 (bf16,
-// normal data) the kernel takes 13.5-14.6 ms by card, 1175-1275 TFLOP/s, with
-// the chip clocked down to ~1.65 GHz; with all-zero operands the same launch (two 64-token
-// stages) takes 11.7 ms at 2.38 GHz, without its operand loads 7.6 ms, and with
-// the loads and LDS reads but no MFMA 11.5 ms.  Before the operand reads
-// crossed the barrier: 14.5 ms where it now takes 13.5.  Barrier crossing with
-// two 64-token stages: 13.7 ms; five 32-token stages 1% slower than four; 4 waves of 128 x 128
-// parts, which read a third less LDS, 15.3 ms (one wave per SIMD leaves the
-// barrier uncovered).
+// normal data) the kernel takes 13.3-14.8 ms by card, 1160-1295 TFLOP/s, with
+// the chip clocked down to ~1.6 GHz; a form of two 64-token stages takes 11.7 ms
+// at 2.38 GHz with all-zero operands, 7.6 ms without its operand loads, and 11.5
+// ms with the loads and LDS reads but no MFMA.  On one card: operand reads that
+// do not cross the barrier 14.5 ms, this form 13.5, two 64-token stages 13.7,
+// five 32-token stages 1% slower than four, 4 waves of 128 x 128 parts, which
+// read a third less LDS, 15.3 (one wave per SIMD leaves the barrier uncovered).
 // Tiles are numbered so that the blocks one XCD runs at a time share a few
 // row tiles and a window of column tiles (its L2 holds their slices).
 
